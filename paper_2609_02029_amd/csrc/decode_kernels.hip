@@ -186,6 +186,7 @@ int decode_workgroup_target(int fmt, int D, int G) {
                           : std::min(kDecodeWgPerCuX4, 4 * split_waves_per_eu(D, G, fmt));
   return std::max(1, per_cu4 * device_cus() / 4);
 }
+int device_cu_count() { return device_cus(); }
 int decode_combine_blocks_per_item(int D, int G) {
   return G * (D / (kCombineChan < D ? kCombineChan : D));
 }

@@ -155,7 +155,29 @@ struct PrefillAttnArgs {
   int32_t n_sinks;
   int32_t n_col_blocks;          // per head: ceil(n_tokens * G / columns)
   float scale_log2;              // scale * log2(e)
+  // Split keys: the r-th head of head_order has workgroups [wg_begin[r],
+  // wg_begin[r + 1]), split by split, each split over the column blocks from
+  // the last token down; split j of a column block adds its key tiles
+  // [j T, (j + 1) T), T = tiles_per_split, and a block of more than T tiles
+  // leaves one partial per split for prefill_merge (workgroup w: acc rows
+  // part_acc[w][column][D], (m, l) pairs part_ml[w][column][2], m in base-2
+  // logit units).
+  int32_t wg_begin[kMaxItems + 1];   // INT32_MAX past the last head's end
+  int32_t tiles_per_split;
+  float *part_acc, *part_ml;
 };
+
+// Keys per tile: 64, or 32 at head_dim 256 (four tiles fit LDS).
+__host__ __device__ constexpr int prefill_keys(int D) { return D > 128 ? 32 : 64; }
+// Tiles of KT keys of a column block whose tokens sit at positions [ta, tb],
+// under S sinks and window W (0 = full): the key ranges are [0, tb + 1) in
+// one, or the sinks [0, S) and the window's keys [ta + 1 - W, tb + 1) where
+// they are disjoint.
+__host__ __device__ inline int prefill_tiles(int KT, int ta, int tb, int S, int W) {
+  const int lo = W == 0 || ta + 1 - W < 0 ? 0 : ta + 1 - W;
+  if (lo <= S) return (tb + KT) / KT;
+  return (S + KT - 1) / KT + (tb - lo + KT) / KT;
+}
 
 #ifndef HWKV_PREFILL_WAVES
 #define HWKV_PREFILL_WAVES 8
@@ -217,6 +239,9 @@ hipError_t launch_stage_chunk(int D, const StageChunkArgs &a, hipStream_t s);
 int prefill_attn_columns_per_block();   // (token, q head) columns
 // f16: the cache, k and v hold binary16 values (else bf16); q is bf16.
 hipError_t launch_prefill_attn(int D, bool f16, const PrefillAttnArgs &a, hipStream_t s);
+// Merges the split partials of launch_prefill_attn into the output rows.
+hipError_t launch_prefill_merge(int D, const PrefillAttnArgs &a, hipStream_t s);
+int device_cu_count();           // compute units of the current device
 
 // Calibration scores: for every (row, q head), the stabilised cosine of each
 // candidate output against the full one (and of the full one against a

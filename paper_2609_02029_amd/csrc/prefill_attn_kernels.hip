@@ -15,7 +15,7 @@
 //
 // Formulation.  A workgroup owns one KV head and 32 * NW consecutive
 // (token, q-head) columns of that head (column c = token * G + g), one
-// 32-column block per wavefront.  Per key tile of 32 positions it computes
+// 32-column block per wavefront.  Per block of 32 key positions it computes
 //     S^T = K Q^T           (v_mfma_f32_32x32x16_bf16, K from LDS, Q^T held
 //                            in registers for the whole kernel)
 //     O^T += V^T P^T        (V^T from LDS by transposing reads, P^T straight
@@ -27,12 +27,35 @@
 // key 16*step + 8*(j/4) + 4*half + j%4, exactly the rows a lane already
 // holds), and the V^T operand is read in that key order.
 //
+// Schedule (prefill_attn).  A tile is two such blocks (one at head_dim 256),
+// and a wavefront's tile takes two phases: the products -- S^T of tile i
+// alternating with V^T P^T of tile i - 1 -- and the softmax of tile i.  The
+// eight wavefronts are two groups, one of each on every SIMD, that run the
+// phases in turn, a barrier apart: while one keeps the matrix cores busy the
+// other has the vector ALU.  (With every wavefront in the same phase, as the
+// barrier per tile of a plain loop leaves them, the two units take turns.)
+// Measured on one chip, before -> after, 8K tokens at 120K of context, head_dim
+// 256, windows {2K, 8K, 32K, full}: 7.30 -> 6.67 ms, 1,170 -> 1,285 TFLOP/s
+// (the matrix cores busy 0.60 -> 0.73 of the cycles, at a clock that falls
+// with the load); 4K tokens at 12K, head_dim 64, binary16: 508 -> 329 us, bound
+// by the exponentials and the arithmetic around them.  The softmax phase also
+// issues the loads of tile i + 2 into the fourth stage of LDS; tile addresses
+// are kept as runs (issue_loads), since a lane's address worked out per tile
+// cost as much as a third of the softmax.
+//
+// Split keys.  A launch of few column blocks (a short chunk over a long
+// context), or with most of its keys in one head, leaves CUs idle: the host
+// then splits the key tiles of every block over several workgroups
+// (tiles_per_split), whose partials prefill_merge adds up.  512 tokens at 48K
+// of context, head_dim 128: 1,717 -> 153 us with both changes (206 by this
+// one); 1,999 tokens at 30K over fp8, head_dim 256: 1,450 -> 672 (801).
+//
 // Data movement.  K and V tiles go from global memory straight into LDS
-// (global_load_lds_dwordx4: lane i of an instruction fills bytes
+// (buffer_load_dwordx4 ... lds: lane i of an instruction fills bytes
 // [16i, 16i + 16) of the instruction's LDS block; each lane picks its own
-// source), double-buffered, one barrier per tile, no staging registers.
-// Both tiles are stored as rows of one 16-byte channel chunk for the 32
-// keys (512 B), two rows per load instruction; in odd rows key k sits at
+// source), in four stages (two in the calibration replay), no staging
+// registers.  Both are stored as rows of one 16-byte channel chunk for the 32
+// keys of a block (512 B), two rows per load instruction; in odd rows key k sits at
 // position k ^ 4.  Lane L of every load then fetches key (L % 32) ^
 // (4 (L / 32)) -- one key per lane and tile, so its cache slot and row
 // addresses are worked out once per tile -- at chunk 2n + L / 32.
@@ -63,7 +86,9 @@
 // moves when a tile's maximum exceeds it by more than 8 (log2 units), so the
 // O^T accumulators are rescaled rarely; any shift gives the same quotient
 // and terms stay below 2^8.  Tiles no column of a wavefront can see are
-// skipped by that wavefront; tiles every column sees skip the mask.
+// skipped by that wavefront; tiles every column sees whole skip the mask.
+#include <type_traits>
+
 #include "hwkv_internal.h"
 
 namespace hwkv {
@@ -84,13 +109,8 @@ typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-constexpr int kKeys = 32;                  // keys per tile
-// Operand reads from LDS issued ahead of the products (sched_group_barrier
-// masks: matrix-core instructions, LDS reads)
-constexpr int kPipeK = 4;                  // K operands (one 16-byte read each)
-constexpr int kPipeV = 3;                  // V operands (two 8-byte reads each)
-constexpr int kSchedMfma = 0x008;
-constexpr int kSchedDsRead = 0x100;
+constexpr int kKeys = 32;                  // keys per product block
+constexpr int kPipe = 2;                   // operand reads ahead of their products
 
 __device__ __forceinline__ u32x4_t ld16(const uint16_t *p) {
   return *reinterpret_cast<const u32x4_t *>(p);
@@ -121,6 +141,54 @@ __device__ __forceinline__ f32x16_t mfma16(u32x4_t a, u32x4_t b, f32x16_t c) {
 __device__ __forceinline__ void g2lds(const void *src, uint8_t *lds_block) {
   __builtin_amdgcn_global_load_lds(src, (lds_void_t *)lds_block, 16, 0, 0);
 }
+
+// The same at a scalar base and 32-bit byte offsets (lane's and uniform).  The
+// descriptor spans 2^31 bytes (a unit's K or V is smaller); an access is out
+// of range, and reads as zero, where the lane's offset is at or past the span
+// less the uniform offset, so a lane offset of the span itself always is.
+constexpr uint32_t kSpan = 0x80000000u;
+constexpr int kNoRow = (int)kSpan;
+typedef u32x4_t rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const void *base) {
+  const uint64_t u = (uint64_t)base;
+  return rsrc_t{(uint32_t)u, (uint32_t)(u >> 32) & 0xffffu, kSpan, 0x00020000u};
+}
+__device__ __forceinline__ const uint8_t *scalar_ptr(const void *p) {
+  const uint64_t u = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+  return (const uint8_t *)(((uint64_t)hi << 32) | lo);
+}
+// The load has no destination register, and the kernel waits for it itself
+// (wait_loads, then a barrier).  As a builtin it would make the compiler wait
+// for every load in flight before each transposing read of LDS, the next
+// tiles' loads among them, which are to stay in flight.
+__device__ __forceinline__ void b2lds(rsrc_t r, uint8_t *lds_block, int voffset,
+                                      int soffset) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(
+          (uint32_t)(uintptr_t)(lds_void_t *)lds_block),
+      "v"(voffset), "s"(r), "s"(soffset)
+      : "memory", "m0");
+}
+
+// The larger of two numbers, NaN if either is: pairs of these are one
+// v_maximum3_f32, where fmaxf first quiets every operand with an instruction
+// of its own (a product's result is not known to be a quiet number).
+__device__ __forceinline__ float max_of(float x, float y) {
+  return __builtin_elementwise_maximum(x, y);
+}
+
+// The lane index, worked out where it is used: what follows from it does not
+// stay live in vector registers between uses.
+__device__ __forceinline__ int lane_now() {
+  int x = threadIdx.x & 63;
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// no instruction moves across this point
+__device__ __forceinline__ void pin() { __builtin_amdgcn_sched_barrier(0); }
 
 __device__ __forceinline__ void wait_loads() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -153,11 +221,22 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void prefill_attn(const PrefillAttnArgs a) {
   using P = Prefill<D, NW>;
   constexpr int KS = P::KS, DB = P::DB, DC = P::DC;
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * P::STAGE];
+  constexpr int KT = prefill_keys(D);               // keys per tile
+  constexpr int U = KT / kKeys;                     // blocks of 32 keys per tile
+  constexpr int NH = NW / U;                        // waves loading each block
+  constexpr int IPW = P::NINST / NH;                // loads per wave and tile, each of K, V
+  constexpr int STAGES = 4;
+  static_assert(NW == 8 && P::NINST % NH == 0, "two groups of waves; tile loads");
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[STAGES * U * P::STAGE];
 
   const int nb = a.n_col_blocks;
-  const int h = a.head_order[blockIdx.x / nb];
-  const int cb = nb - 1 - (int)(blockIdx.x % nb);   // later tokens first
+  const int blk = blockIdx.x;
+  // the head: the number of heads that begin at or before this workgroup
+  const int rank = __builtin_amdgcn_readfirstlane(
+      __popcll(__ballot(a.wg_begin[threadIdx.x & 63] <= blk)) - 1);
+  const int split = (blk - a.wg_begin[rank]) / nb;
+  const int h = a.head_order[rank];
+  const int cb = nb - 1 - (blk - a.wg_begin[rank]) % nb;   // later tokens first
   const PrefillAttnHead &hd = a.head[h];
   const int G = a.group;
   const int Hq = a.n_kv_heads * G;
@@ -188,13 +267,7 @@ void prefill_attn(const PrefillAttnArgs a) {
   const bool col_ok = c <= c_last;
   const int cc = min(c, c_last);
   const int tl = cc / G, g = cc - tl * G;
-  const int t = pos(tl);
   const size_t q_row = ((size_t)tl * Hq + (size_t)h * G + g) * D;
-
-  u32x4_t qv[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
-    qv[ks] = col_ok ? ld16(a.q + q_row + 16 * ks + 8 * half) : u32x4_t{0, 0, 0, 0};
 
   // key ranges: [0, ra1) then [rb0, rb1)
   const int lo = (W == 0) ? 0 : max(0, ta + 1 - W);
@@ -206,90 +279,148 @@ void prefill_attn(const PrefillAttnArgs a) {
     rb0 = lo;
     rb1 = tb + 1;
   }
-  const int na = (ra1 + kKeys - 1) / kKeys;
-  const int ntiles = na + (rb1 - rb0 + kKeys - 1) / kKeys;
+  const int na = (ra1 + KT - 1) / KT;
+  const int ntiles = na + (rb1 - rb0 + KT - 1) / KT;   // prefill_tiles(ta, tb, S, W)
+  // this split's tiles (uniform; a shorter block has fewer splits)
+  const int i_lo = split * a.tiles_per_split;
+  if (i_lo >= ntiles) return;
+  const int n_it = min(ntiles - i_lo, a.tiles_per_split);
+
+  u32x4_t qv[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+    qv[ks] = col_ok ? ld16(a.q + q_row + 16 * ks + 8 * half) : u32x4_t{0, 0, 0, 0};
 
   const uint16_t *kc = a.cache + hd.k_off;
   const uint16_t *vc = a.cache + hd.v_off;
   const size_t in_stride = (size_t)a.n_kv_heads * D;
   const uint16_t *kin = a.k + (size_t)h * D;
   const uint16_t *vin = a.v + (size_t)h * D;
-  const uint16_t *zero = reinterpret_cast<const uint16_t *>(g_zero_row);
 
-  auto tile_range = [&](int i, int *s0, int *se) {
-    if (i < na) {
-      *s0 = i * kKeys;
-      *se = ra1;
-    } else {
-      *s0 = rb0 + (i - na) * kKeys;
-      *se = rb1;
-    }
+  auto tile_range = [na, ra1, rb0, rb1](int i, int *s0, int *se) {
+    const bool first = i < na;
+    *s0 = first ? i * KT : rb0 + (i - na) * KT;
+    *se = first ? ra1 : rb1;
   };
 
-  // The key this lane loads in every tile.
-  const int lkey = cl ^ (4 * half);
-  // Ring slot of the load tile's positions: positions s >= b0 = max(s0, S)
-  // sit at S + (rb + s - b0) mod W with rb = (b0 - S) mod W; rb follows b0
-  // from tile to tile (b0 never decreases).
-  int ld_b0 = S, ld_rb = 0;
-  auto issue_loads = [&](int i, int buf) {
-    int s0, se;
-    tile_range(i, &s0, &se);
-    const int b0 = max(s0, S);
-    if (W != 0) {
-      const int step = b0 - ld_b0;
-      int rb = ld_rb + step;
-      if (step > kKeys || W < kKeys)
-        rb %= W;                                   // range switch, tiny windows
-      else
-        rb = rb >= W ? rb - W : rb;
-      ld_rb = rb;
-    }
-    ld_b0 = b0;
-    const int s = s0 + lkey;
-    const uint16_t *kp, *vp;
-    int kstep;                                     // elements per K chunk
-    if (s >= se) {
-      kp = zero;
-      vp = zero;
-      kstep = 8;
-    } else if (s >= p0) {
-      kp = kin + (size_t)(s - p0) * in_stride;
-      vp = vin + (size_t)(s - p0) * in_stride;
-      kstep = 8;
-    } else {
-      int sl = s;
-      if (W != 0 && s >= S) {
-        int off = ld_rb + (s - b0);                // < W + 32
-        if (W >= kKeys)
-          off = off >= W ? off - W : off;
-        else
-          off = off % W;                           // tiny windows only
-        sl = S + off;
-      }
-      if (hd.pto >= 0) {
-        // paged full unit: the tile's 32 keys (s0 is a multiple of 32) lie
-        // in page s0 / 256, at rows sl % 256 of it
-        const int64_t pg = a.page_table[hd.pto + (s0 >> 8)];
-        const uint16_t *pk = a.cache + a.pool_off + pg * 2 * kPageTokens * D;
-        const int sp = sl & (kPageTokens - 1);
-        kp = pk + (size_t)((sp >> 6) * DC) * (kTile * 8) + (sp & 63) * 8;
-        vp = pk + (size_t)kPageTokens * D + (size_t)sp * D;
-      } else {
-        kp = kc + (size_t)((sl >> 6) * DC) * (kTile * 8) + (sl & 63) * 8;
-        vp = vc + (size_t)sl * D;
-      }
-      kstep = kTile * 8;
-    }
-    uint8_t *kl = smem + buf * P::STAGE;
-    uint8_t *vl = kl + P::KBYTES;
+  // Wave w loads block w % U of every tile; lkey is the key of the block this
+  // lane loads.
+  const int lblk = wave % U, ln = wave / U;
+  // Tile loads go by runs: consecutive tiles whose keys follow one another in
+  // the chunk's rows or in cache slots, so that a tile costs two additions to
+  // scalar bases.  K and V bases of the next tile of the run, their steps to
+  // the tile after it (K steps alternate between kstep and kper - kstep: a
+  // 32-key tile is half a 64-slot K tile), the lane's byte offsets (of even and
+  // odd tiles for K) and the bytes from one load's K rows to the next's.
+  int run = 0;                                      // tiles left in the run
+  const uint8_t *run_k = nullptr, *run_v = nullptr;
+  int kstep = 0, kper = 0, vstep = 0, kn = 0;
+  int ko = 0, ko2 = 0, vo = 0;
+  constexpr int TB = kTile * D * 2;                 // bytes of a K tile
+  auto put = [&](const uint8_t *kb, const uint8_t *vb, int ko, int vo, int kn, uint8_t *stage) {
+    const rsrc_t kr = make_rsrc(scalar_ptr(kb)), vr = make_rsrc(scalar_ptr(vb));
+    kn = __builtin_amdgcn_readfirstlane(kn);
+    uint8_t *kl = stage + lblk * P::STAGE + ln * 1024;
+    uint8_t *vl = stage + lblk * P::STAGE + P::KBYTES + ln * P::VPAIR;
 #pragma unroll
-    for (int j = 0; j < P::IPW; ++j) {
-      const int n = wave + j * NW;
-      if (P::NINST % NW != 0 && n >= P::NINST) break;   // uniform per wave
-      const int ch = 2 * n + half;
-      g2lds(kp + ch * kstep, kl + n * 1024);
-      g2lds(vp + ch * 8, vl + n * P::VPAIR);
+    for (int j = 0; j < IPW; ++j) {                 // chunk rows 2n, 2n + 1, n = ln + j NH
+      b2lds(kr, kl + j * NH * 1024, ko, (ln + j * NH) * kn);
+      b2lds(vr, vl + j * NH * P::VPAIR, vo, (ln + j * NH) * 32);
+    }
+  };
+  const uint8_t *const kcb = reinterpret_cast<const uint8_t *>(kc);
+  const uint8_t *const vcb = reinterpret_cast<const uint8_t *>(vc);
+  // the page of position s0 of a paged unit (scalar loads: the table does not
+  // change under the kernel)
+  auto page_of = [&](int s0) -> const uint8_t * {
+    const int pg = ((const __attribute__((address_space(4))) int32_t *)
+                        a.page_table)[__builtin_amdgcn_readfirstlane(hd.pto + (s0 >> 8))];
+    return reinterpret_cast<const uint8_t *>(a.cache + a.pool_off + (int64_t)pg * 2 * kPageTokens * D);
+  };
+  auto issue_loads = [&](int it, uint8_t *stage) {
+    if (run == 0) {
+      const int half = lane_now() >> 5, lkey = (lane_now() & 31) ^ (4 * half);
+      int s0, se;
+      tile_range(i_lo + it, &s0, &se);
+      s0 += kKeys * lblk;                           // the block's first key
+      const int ce = min(p0, se);                   // keys [s0, ce) are cached
+      int sl0 = s0, len = 0;                        // first slot and slots in a row
+      const uint8_t *kb = kcb, *vb = vcb;
+      if (s0 >= p0) {
+        len = se - s0;
+      } else if (W == 0) {
+        len = ce - s0;
+        if (hd.pto >= 0) {
+          kb = page_of(s0);
+          vb = kb + kPageTokens * D * 2;
+          sl0 = s0 & (kPageTokens - 1);
+          len = min(len, kPageTokens - sl0);
+        }
+      } else if (s0 >= S) {
+        const int rb = (s0 - S) % W;
+        sl0 = S + rb;
+        len = min(ce - s0, W - rb);
+      }
+      if (len >= kKeys) {
+        run = __builtin_amdgcn_readfirstlane((len - kKeys) / KT + 1);
+        if (s0 >= p0) {
+          const size_t at = (size_t)(s0 - p0) * in_stride;
+          run_k = scalar_ptr(kin + at);
+          run_v = scalar_ptr(vin + at);
+          vstep = kstep = __builtin_amdgcn_readfirstlane(KT * (int)in_stride * 2);
+          kper = 2 * kstep;
+          ko = ko2 = vo = lkey * (int)in_stride * 2 + half * 16;
+          kn = 32;
+        } else {
+          // slots sl0 + lkey: K tile and slot within it by the lane, tiles
+          // 64 slots apart
+          run_k = scalar_ptr(kb + (size_t)(sl0 >> 6) * TB);
+          run_v = scalar_ptr(vb + (size_t)sl0 * (D * 2));
+          const int x = (sl0 & 63) + lkey, y = x + (KT & 63);
+          ko = (x >> 6) * TB + (x & 63) * 16 + half * 1024;
+          ko2 = (y >> 6) * TB + (y & 63) * 16 + half * 1024;
+          kstep = KT < kTile ? 0 : TB;
+          kper = KT < kTile ? TB : 2 * TB;
+          vstep = KT * D * 2;
+          vo = lkey * D * 2 + half * 16;
+          kn = 2048;
+        }
+      } else {
+        // a block that is not one run, key by key: keys below p0 (and, as
+        // zeros, those past the range) from the cache, the others from the
+        // chunk
+        const int s = s0 + lkey;
+        const bool own = s >= p0 && s < se;
+        if (s0 + kKeys > p0 && s0 < se) {
+          const int c0 = max(s0, p0);
+          const size_t at = (size_t)(c0 - p0) * in_stride;
+          const int off = (s - c0) * (int)in_stride * 2 + half * 16;
+          if (own)
+            put(reinterpret_cast<const uint8_t *>(kin + at),
+                reinterpret_cast<const uint8_t *>(vin + at), off, off, 32, stage);
+        }
+        int sl = s;
+        if (W != 0 && s >= S) sl = S + (s - S) % W;
+        if (hd.pto >= 0) {
+          sl &= kPageTokens - 1;
+          if (s0 >= ce) kb = kcb;                   // no cached key: nothing is read
+        }
+        const bool cached = s < ce;
+        if (!own)
+          put(kb, vb, cached ? (sl >> 6) * TB + (sl & 63) * 16 + half * 1024 : kNoRow,
+              cached ? sl * (D * 2) + half * 16 : kNoRow, 2048, stage);
+        return;
+      }
+    }
+    put(run_k, run_v, ko, vo, kn, stage);
+    --run;
+    run_k = scalar_ptr(run_k + kstep);
+    run_v = scalar_ptr(run_v + vstep);
+    kstep = __builtin_amdgcn_readfirstlane(kper - kstep);
+    if constexpr (KT < kTile) {
+      const int x = ko;
+      ko = ko2;
+      ko2 = x;
     }
   };
 
@@ -340,7 +471,7 @@ void prefill_attn(const PrefillAttnArgs a) {
     for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
 
   // S^T operand: key cl of chunk row 2ks + half (odd rows swizzled).
-  const int klane = half * 512 + lkey * 16;
+  int klane = half * 512 + (cl ^ (4 * half)) * 16;
   // V^T operand: 16-lane group gq = lane / 16, local lane mq.  For k-step s
   // and half hh of its 8 keys, lane (gq, mq) reads 8 bytes of key
   // 16s + 8hh + 4(gq / 2) + mq / 4 at channel 32db + 16(gq % 2) + 4(mq % 4),
@@ -348,50 +479,23 @@ void prefill_attn(const PrefillAttnArgs a) {
   const int gq = lane >> 4, mq = lane & 15;
   const int vpar = (mq >> 1) & 1;
   const int vkey0 = 4 * (gq >> 1) + (mq >> 2);
-  const int vlane = (gq & 1) * P::VPAIR + vpar * 512 + (vkey0 ^ (4 * vpar)) * 16 + (mq & 1) * 8;
+  int vlane = P::KBYTES + (gq & 1) * P::VPAIR + vpar * 512 + (vkey0 ^ (4 * vpar)) * 16 +
+              (mq & 1) * 8;
+  // one register each, not the terms of their sums (the 256-channel kernel
+  // has none to spare)
+  asm volatile("" : "+v"(klane), "+v"(vlane));
 
-  issue_loads(0, 0);
-
-  for (int i = 0; i < ntiles; ++i) {
-    wait_loads();
-    __syncthreads();
-    if (i + 1 < ntiles) issue_loads(i + 1, (i + 1) & 1);
-    int s0, se;
-    tile_range(i, &s0, &se);
+  // masks the block of keys from s0 on, unless every column sees all of it
+  auto mask = [&](f32x16_t &st, int s0, int se) {
     const int slast = min(s0 + kKeys, se) - 1;
-    const bool skip = !wave_live || s0 > t_hi ||
-                      (W != 0 && s0 >= S && slast < t_lo + 1 - W);
-    if (skip) continue;
-    const uint8_t *kl = smem + (i & 1) * P::STAGE + klane;
-    const uint8_t *vl = smem + (i & 1) * P::STAGE + P::KBYTES + vlane;
-    f32x16_t st;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) st[r] = 0.0f;
-    {
-      u32x4_t kx[KS];
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kx[ks] = *reinterpret_cast<const u32x4_t *>(kl + ks * 1024);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) st = mfma16<F16>(kx[ks], qv[ks], st);
-      // K operand reads run kPipeK products ahead of their use (left to
-      // itself the scheduler reads each operand just before its product and
-      // waits out the LDS latency every time)
-      constexpr int PK = kPipeK < KS ? kPipeK : KS;
-      __builtin_amdgcn_sched_group_barrier(kSchedDsRead, PK, 0);
-#pragma unroll
-      for (int i = 0; i < KS - PK; ++i) {
-        __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(kSchedMfma, PK, 0);
-    }
     const bool full_vis = s0 + kKeys <= se && slast <= t_lo &&
                           (W == 0 || slast < S || s0 >= t_hi + 1 - W);
     if (!full_vis) {
       // key of row r: e + cr, cr = 8 (r / 4) + r % 4; e and e - t are made
       // opaque so the per-row offsets stay compile-time constants on the
       // uniform side of each comparison
-      int e = s0 + 4 * half, d = e - t;
+      const int cx = wc0 + (lane_now() & 31);
+      int e = s0 + 4 * (lane_now() >> 5), d = e - pos(min(cx, c_last) / G);
       asm volatile("" : "+v"(e), "+v"(d));
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -401,14 +505,13 @@ void prefill_attn(const PrefillAttnArgs a) {
         if (!vis) st[r] = -__builtin_inff();
       }
     }
-    float mx = st[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, st[r]);
-    {
-      float lo_half, hi_half;
-      halves(mx, &lo_half, &hi_half);
-      mx = fmaxf(lo_half, hi_half);
-    }
+  };
+  // raises the shift (and rescales the sums) where a block's maximum mx of
+  // this lane half exceeds it by more than 8 in base 2
+  auto raise = [&](float mx) {
+    float lo_half, hi_half;
+    halves(mx, &lo_half, &hi_half);
+    mx = max_of(lo_half, hi_half);
     if (__any(mx > m + tau)) {
       const float mn = fmaxf(m, mx);
       const float alpha = __builtin_amdgcn_exp2f((m - mn) * c2);
@@ -419,57 +522,177 @@ void prefill_attn(const PrefillAttnArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
     }
-    const float mc = m * c2 - pbias;
-    float pr[16];
+  };
+  // The products of a phase: S^T of a tile (K at kl) and, if VALUES, O^T +=
+  // V^T P^T of the one before it (V at vl; 16 keys a step, two steps a block).
+  // They alternate, and so do the two blocks of S^T: a product that
+  // adds to the one before it would wait out that one's latency.  The order
+  // of operand reads and products is pinned, reads kPipe products of their
+  // kind ahead: left to itself the scheduler reads each operand just before
+  // its product and waits out the LDS latency every time.
+  constexpr int N = U * KS;                      // products of each kind
+  static_assert(N == 2 * U * DB, "as many products of both kinds");
+  auto products = [&](auto values, f32x16_t (&st)[U], const u32x4_t (&pb)[2 * U],
+                      const uint8_t *kl, const uint8_t *vl) {
+    constexpr bool VALUES = decltype(values)::value;
+    constexpr int A = VALUES ? kPipe : 2 * kPipe;
+    u32x4_t kx[A], va[A];
+    auto read_k = [&](int i) {
+      kx[i % A] = *reinterpret_cast<const u32x4_t *>(kl + (i % U) * P::STAGE + (i / U) * 1024);
+    };
+    auto read_v = [&](int i) {
+      const int s = i / DB, db = i % DB;
+      i16x4_t v2[2];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      pr[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[r], c2, -mc));
-      l += pr[r];
+      for (int hh = 0; hh < 2; ++hh)
+        v2[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_i16x4_t *)(vl + (s / 2) * P::STAGE + 2 * db * P::VPAIR +
+                            (16 * (s % 2) + 8 * hh) * 16));
+      va[i % A] = __builtin_bit_cast(
+          u32x4_t, __builtin_shufflevector(v2[0], v2[1], 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
+      read_k(i);
+      if constexpr (VALUES) read_v(i);
     }
-    u32x4_t pb[2];
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int i = 0; i < N; ++i) {
+      if (i < U)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        pb[s][j] = F16 ? pack_f16(pr[8 * s + 2 * j], pr[8 * s + 2 * j + 1])
-                       : pack_bf16(pr[8 * s + 2 * j], pr[8 * s + 2 * j + 1]);
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        i16x4_t v2[2];
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-          v2[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (lds_i16x4_t *)(vl + 2 * db * P::VPAIR + (16 * s + 8 * hh) * 16));
-        const u32x4_t va = __builtin_bit_cast(
-            u32x4_t, __builtin_shufflevector(v2[0], v2[1], 0, 1, 2, 3, 4, 5, 6, 7));
-        o[db] = mfma16<F16>(va, pb[s], o[db]);
+        for (int r = 0; r < 16; ++r) st[i % U][r] = 0.0f;
+      pin();
+      st[i % U] = mfma16<F16>(kx[i % A], qv[i / U], st[i % U]);
+      pin();
+      if (i + A < N) read_k(i + A);
+      if constexpr (VALUES) {
+        pin();
+        o[i % DB] = mfma16<F16>(va[i % A], pb[i / DB], o[i % DB]);
+        pin();
+        if (i + A < N) read_v(i + A);
       }
     }
-    // V operand reads (two per product) run kPipeV products ahead
-    {
-      constexpr int PV = kPipeV < 2 * DB ? kPipeV : 2 * DB;
-      __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2 * PV, 1);
-#pragma unroll
-      for (int i = 0; i < 2 * DB - PV; ++i) {
-        __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 1);
-        __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 1);
-      }
-      __builtin_amdgcn_sched_group_barrier(kSchedMfma, PV, 1);
-    }
+    pin();
+  };
+  // Tiles [f0, f0 + fn) of this split are seen whole by every column of the
+  // wave.
+  int f0, f1;
+  {
+    const int base = lo <= S ? 0 : rb0, tile0 = lo <= S ? 0 : na;   // of the range holding t_lo
+    f1 = tile0 + max(0, t_lo + 1 - base) / KT;
+    f0 = tile0 + (W == 0 ? 0 : (max(0, t_hi + 1 - W - base) + KT - 1) / KT);
+    f0 = max(f0 - i_lo, 0);
+    f1 = wave_live ? f1 - i_lo : f0;
   }
+  const uint32_t fn = (uint32_t)max(f1 - f0, 0);
+  // whether any column of this wave sees a key of tile it
+  auto visible = [&](int it) {
+    int s0, se;
+    tile_range(i_lo + it, &s0, &se);
+    const int slast = min(s0 + KT, se) - 1;
+    return wave_live && s0 <= t_hi && !(W != 0 && s0 >= S && slast < t_lo + 1 - W);
+  };
+  // every wave's LDS reads are done and the loads it waited for are in LDS
+  auto phase_end = [&]() {
+    asm volatile("" ::: "memory");
+    pin();
+    __builtin_amdgcn_s_barrier();
+    pin();
+    asm volatile("" ::: "memory");
+  };
+
+  // q has arrived before the loop: a wait for it inside would wait for the
+  // tiles' loads too
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qv[ks]));
+  constexpr int SB = U * P::STAGE;               // bytes of a stage
+  issue_loads(0, smem);
+  if (n_it > 1) issue_loads(1, smem + SB);
+  wait_loads();
+  phase_end();
+  const bool late = wave >= NW / 2;              // the second group
+  if (late) phase_end();
+
+  f32x16_t st[U];                                // S^T of the tile
+  u32x4_t pb[2 * U];                             // the weights of the tile, packed
+  bool held = false;                             // pb holds weights to add
+  int so = 0, so1 = 0;                           // LDS offsets of tiles it, it - 1
+  for (int it = 0;; ++it) {
+    // ---- products: S^T of tile it, then V^T P^T of tile it - 1
+    const bool whole = (uint32_t)(it - f0) < fn;
+    const bool vis = it < n_it && (whole || visible(it));
+    __builtin_amdgcn_s_waitcnt(0xc07f);          // no scalar load outstanding: LDS waits can count
+    const uint8_t *kl = smem + so + klane, *vl = smem + so1 + vlane;
+    if (held)                                    // (S^T goes unused where !vis)
+      products(std::true_type{}, st, pb, kl, vl);
+    else if (vis)
+      products(std::false_type{}, st, pb, kl, vl);
+    wait_loads();                                // tile it + 1, issued a phase ago
+    if (it == n_it) break;
+    phase_end();
+    // ---- softmax of tile it
+    if (it + 2 < n_it) issue_loads(it + 2, smem + (so >= 2 * SB ? so - 2 * SB : so + 2 * SB));
+    held = vis;
+    if (vis) {
+      if (!whole) {
+        int s0, se;
+        tile_range(i_lo + it, &s0, &se);
+#pragma unroll
+        for (int u = 0; u < U; ++u) mask(st[u], s0 + kKeys * u, se);
+      }
+      float mx = max_of(st[0][0], st[0][1]);
+#pragma unroll
+      for (int r = 2; r < 16 * U; r += 2)
+        mx = max_of(max_of(mx, st[r / 16][r % 16]), st[r / 16][r % 16 + 1]);
+      raise(mx);
+      // every weight before the sums and the packing, which would otherwise
+      // each wait for its exponential
+      const float mc = m * c2 - pbias;
+#pragma unroll
+      for (int r = 0; r < 16 * U; ++r)
+        st[r / 16][r % 16] = __builtin_fmaf(st[r / 16][r % 16], c2, -mc);
+      pin();
+#pragma unroll
+      for (int r = 0; r < 16 * U; ++r)
+        st[r / 16][r % 16] = __builtin_amdgcn_exp2f(st[r / 16][r % 16]);
+      pin();
+      float ls[4] = {l, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int r = 0; r < 16 * U; r += 2) {
+        const float w0 = st[r / 16][r % 16], w1 = st[r / 16][r % 16 + 1];
+        ls[r % 4] += w0;
+        ls[r % 4 + 1] += w1;
+        pb[r / 8][r % 8 / 2] = F16 ? pack_f16(w0, w1) : pack_bf16(w0, w1);
+      }
+      l = (ls[0] + ls[1]) + (ls[2] + ls[3]);
+    }
+    so1 = so;
+    so = so == (STAGES - 1) * SB ? 0 : so + SB;
+    phase_end();
+  }
+  if (!late) phase_end();
 
   float l_lo, l_hi;
   halves(l, &l_lo, &l_hi);
-  if (!col_ok) return;
+  // the lane's column and output row, recomputed rather than kept live
+  // through the loop
+  const int c_out = wc0 + (lane_now() & 31);
+  const int half_o = lane_now() >> 5;
+  if (c_out > c_last) return;
   const float lt = l_lo + l_hi;
-  const float inv = hd.v_scale / lt;     // the stored values' scale (fp8)
-  // the output row, recomputed here rather than kept live through the loop
-  int c_out = c;
-  asm volatile("" : "+v"(c_out));
-  const int tl_o = c_out / G, g_o = c_out - tl_o * G;
-  float *orow = a.out + ((size_t)tl_o * Hq + (size_t)h * G + g_o) * D;
+  float inv;
+  float *orow;
+  if (n_it == ntiles) {
+    inv = hd.v_scale / lt;               // the stored values' scale (fp8)
+    const int tl_o = c_out / G, g_o = c_out - tl_o * G;
+    orow = a.out + ((size_t)tl_o * Hq + (size_t)h * G + g_o) * D;
+  } else {
+    inv = 1.0f;
+    const size_t pc = (size_t)blk * (32 * NW) + (c_out - c_first);
+    orow = a.part_acc + pc * D;
+    if (half_o == 0)
+      *reinterpret_cast<float2 *>(a.part_ml + pc * 2) = make_float2(fmaxf(m * c2, -3e38f), lt);
+  }
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -479,10 +702,83 @@ void prefill_attn(const PrefillAttnArgs a) {
       v.y = o[db][4 * rq + 1] * inv;
       v.z = o[db][4 * rq + 2] * inv;
       v.w = o[db][4 * rq + 3] * inv;
-      *reinterpret_cast<float4 *>(orow + 32 * db + 8 * rq + 4 * half) = v;
+      *reinterpret_cast<float4 *>(orow + 32 * db + 8 * rq + 4 * half_o) = v;
     }
 }
 
+// Merge of the split partials: one row of D / 4 lanes per column, a lane
+// owning 4 channels.  A column block of more than tiles_per_split tiles has
+// one partial per split; out = sum acc_j 2^(m_j - M) / sum l_j 2^(m_j - M),
+// M = max m_j (a split in which the column sees no key has m = -1e30 logit
+// units and zero sums), times the V scale.  Bound by reading the partials.
+constexpr int kMergeUnroll = 4;
+template <int D, int NW>
+__global__ __launch_bounds__(256) void prefill_merge(const PrefillAttnArgs a) {
+  constexpr int LPC = D / 4;                       // lanes per column
+  constexpr int CPW = 256 / LPC;                   // columns per workgroup
+  constexpr int COLS = 32 * NW;                    // columns per block
+  constexpr int PER = COLS / CPW;                  // workgroups per block
+  const int nb = a.n_col_blocks;
+  const int rank = blockIdx.x / (nb * PER);
+  const int x = blockIdx.x % (nb * PER);
+  const int cb = x / PER;
+  const int G = a.group, Hq = a.n_kv_heads * G;
+  const int c_first = cb * COLS;
+  const int c_last = min(c_first + COLS, a.n_tokens * G) - 1;
+  const int h = a.head_order[rank];
+  const int T = a.tiles_per_split;
+  const int nt = prefill_tiles(prefill_keys(D), a.p0 + c_first / G, a.p0 + c_last / G, a.n_sinks, a.head[h].window);
+  if (nt <= T) return;                             // uniform: written by its one split
+  const int ns = (nt + T - 1) / T;
+  const int col = x % PER * CPW + threadIdx.x / LPC;   // column of the block
+  const int c = c_first + col;
+  if (c > c_last) return;
+  const int ch = threadIdx.x % LPC * 4;
+  // split j's workgroup is w0 + j nb
+  const size_t w0 = (size_t)a.wg_begin[rank] + (nb - 1 - cb);
+  const float *acc = a.part_acc + (w0 * COLS + col) * D + ch;
+  const float *ml = a.part_ml + (w0 * COLS + col) * 2;
+  const size_t step = (size_t)nb * COLS;
+  float M = -INFINITY, L = 0.0f;
+  float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int j0 = 0; j0 < ns; j0 += kMergeUnroll) {
+    float2 s[kMergeUnroll];
+    float4 v[kMergeUnroll];
+#pragma unroll
+    for (int u = 0; u < kMergeUnroll; ++u) {       // every load of the round in flight
+      const size_t j = (size_t)min(j0 + u, ns - 1);
+      s[u] = *reinterpret_cast<const float2 *>(ml + j * step * 2);
+      v[u] = *reinterpret_cast<const float4 *>(acc + j * step * D);
+    }
+    float Mn = M;
+#pragma unroll
+    for (int u = 0; u < kMergeUnroll; ++u) {
+      if (j0 + u >= ns) s[u] = make_float2(-INFINITY, 0.0f);
+      Mn = fmaxf(Mn, s[u].x);
+    }
+    const float f = __builtin_amdgcn_exp2f(M - Mn);
+    L *= f;
+    A.x *= f;
+    A.y *= f;
+    A.z *= f;
+    A.w *= f;
+#pragma unroll
+    for (int u = 0; u < kMergeUnroll; ++u) {
+      if (j0 + u >= ns) break;                     // uniform
+      const float e = __builtin_amdgcn_exp2f(s[u].x - Mn);
+      L += s[u].y * e;
+      A.x += v[u].x * e;
+      A.y += v[u].y * e;
+      A.z += v[u].z * e;
+      A.w += v[u].w * e;
+    }
+    M = Mn;
+  }
+  const float inv = a.head[h].v_scale / L;
+  const int tl = c / G, g = c - tl * G;
+  *reinterpret_cast<float4 *>(a.out + ((size_t)tl * Hq + (size_t)h * G + g) * D + ch) =
+      make_float4(A.x * inv, A.y * inv, A.z * inv, A.w * inv);
+}
 
 // Calibration replay in one pass.  Workgroups and columns as in prefill_attn
 // (column c = row * G + g of one KV head, row r at position rows[r]); the
@@ -789,7 +1085,7 @@ void replay_attn(const ReplayAttnArgs a) {
 int prefill_attn_columns_per_block() { return 32 * kPrefillWaves; }
 
 hipError_t launch_prefill_attn(int D, bool f16, const PrefillAttnArgs &a, hipStream_t s) {
-  const dim3 grid((unsigned)(a.n_col_blocks * a.n_kv_heads));
+  const dim3 grid((unsigned)a.wg_begin[a.n_kv_heads]);
   const dim3 block(kPrefillWaves * 64);
 #define HWKV_PA(DD, FF) \
   hipLaunchKernelGGL((prefill_attn<DD, kPrefillWaves, FF>), grid, block, 0, s, a)
@@ -800,6 +1096,18 @@ hipError_t launch_prefill_attn(int D, bool f16, const PrefillAttnArgs &a, hipStr
     default: return hipErrorInvalidValue;
   }
 #undef HWKV_PA
+  return hipGetLastError();
+}
+
+hipError_t launch_prefill_merge(int D, const PrefillAttnArgs &a, hipStream_t s) {
+  const int per = 32 * kPrefillWaves / (256 / (D / 4));   // workgroups per column block
+  const dim3 grid((unsigned)(a.n_col_blocks * a.n_kv_heads * per)), block(256);
+  switch (D) {
+    case 64: hipLaunchKernelGGL((prefill_merge<64, kPrefillWaves>), grid, block, 0, s, a); break;
+    case 128: hipLaunchKernelGGL((prefill_merge<128, kPrefillWaves>), grid, block, 0, s, a); break;
+    case 256: hipLaunchKernelGGL((prefill_merge<256, kPrefillWaves>), grid, block, 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
