@@ -8,10 +8,16 @@
 namespace hwkv {
 
 // Instantiated in the per-format sources.
+extern template hipError_t launch_decode_item_fmt<HWKV_KV_BF16>(int, int, const ItemArgs &,
+                                                                hipStream_t, hipEvent_t, hipEvent_t);
 extern template hipError_t launch_decode_split_fmt<HWKV_KV_BF16>(
     int, int, const DecodeArgs &, int, hipStream_t, hipEvent_t, hipEvent_t);
+extern template hipError_t launch_decode_item_fmt<HWKV_KV_F16>(int, int, const ItemArgs &,
+                                                                hipStream_t, hipEvent_t, hipEvent_t);
 extern template hipError_t launch_decode_split_fmt<HWKV_KV_F16>(
     int, int, const DecodeArgs &, int, hipStream_t, hipEvent_t, hipEvent_t);
+extern template hipError_t launch_decode_item_fmt<HWKV_KV_FP8_E4M3>(int, int, const ItemArgs &,
+                                                                hipStream_t, hipEvent_t, hipEvent_t);
 extern template hipError_t launch_decode_split_fmt<HWKV_KV_FP8_E4M3>(
     int, int, const DecodeArgs &, int, hipStream_t, hipEvent_t, hipEvent_t);
 
@@ -176,7 +182,22 @@ struct CombineLaunch {
   }
 };
 
+template <int D, int G>
+struct ItemMergeLaunch {
+  static hipError_t run(const ItemArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const int rows = a.n_seqs * a.n_kv_heads * G, per = 256 / (D / 4);
+    hipExtLaunchKernelGGL((item_merge<D, G>), dim3((rows + per - 1) / per), dim3(256), 0, s, e0, e1,
+                          0, a);
+    return hipGetLastError();
+  }
+};
+
 }  // namespace
+
+hipError_t launch_item_merge(int D, int G, const ItemArgs &a, hipStream_t s, hipEvent_t e0,
+                             hipEvent_t e1) {
+  return dispatch_dg<ItemMergeLaunch>(D, G, a, s, e0, e1);
+}
 
 int decode_workgroup_target(int fmt, int D, int G) {
   // at most one workgroup per SIMD slot the register budget holds (the fp8
@@ -202,6 +223,16 @@ hipError_t launch_decode_split(int fmt, int D, int G, const DecodeArgs &a,
       return launch_decode_split_fmt<HWKV_KV_FP8_E4M3>(D, G, a, n_splits, s, e0, e1);
     default:
       return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_decode_item(int fmt, int D, int G, const ItemArgs &a, hipStream_t s,
+                              hipEvent_t e0, hipEvent_t e1) {
+  switch (fmt) {
+    case HWKV_KV_BF16: return launch_decode_item_fmt<HWKV_KV_BF16>(D, G, a, s, e0, e1);
+    case HWKV_KV_F16: return launch_decode_item_fmt<HWKV_KV_F16>(D, G, a, s, e0, e1);
+    case HWKV_KV_FP8_E4M3: return launch_decode_item_fmt<HWKV_KV_FP8_E4M3>(D, G, a, s, e0, e1);
+    default: return hipErrorInvalidValue;
   }
 }
 

@@ -826,6 +826,7 @@ hipError_t dispatch_dg(int D, int G, Args &&...args) {
 }  // namespace hwkv
 
 #include "decode_mfma.h"
+#include "decode_item.h"
 
 namespace hwkv {
 namespace {
@@ -848,7 +849,25 @@ struct SplitLaunch {
   };
 };
 
+template <int F>
+struct ItemLaunch {
+  template <int D, int G>
+  struct At {
+    static hipError_t run(const ItemArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+      hipExtLaunchKernelGGL((decode_item<D, G, F>), dim3(a.n_seqs * a.wg_begin[a.n_kv_heads]),
+                            dim3(item_waves(D, G) * 64), 0, s, e0, e1, 0, a);
+      return hipGetLastError();
+    }
+  };
+};
+
 }  // namespace
+
+template <int F>
+hipError_t launch_decode_item_fmt(int D, int G, const ItemArgs &a, hipStream_t s, hipEvent_t e0,
+                                  hipEvent_t e1) {
+  return dispatch_dg<ItemLaunch<F>::template At>(D, G, a, s, e0, e1);
+}
 
 template <int F>
 hipError_t launch_decode_split_fmt(int D, int G, const DecodeArgs &a,

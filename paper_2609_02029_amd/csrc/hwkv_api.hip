@@ -61,6 +61,7 @@ struct hwkv_cache {
   bool timing = false;
   std::vector<hipEvent_t> ev_pool;   // created events, reused
   size_t ev_used = 0;                // events recorded since the last read
+  std::vector<char> ev_merged;       // per launch group since then: has a merge
 };
 
 namespace {
@@ -762,6 +763,150 @@ int scratch_ptr(void **out) {
   return HWKV_OK;
 }
 
+// Tiles per workgroup of a launch of `total` tiles: items of more are split.  A
+// quarter above an even share of the CUs (48 ragged sequences of 200-6,000
+// tokens, 8 KV heads: 84 us a layer with whole items, 78 / 77 at 1.0 / 1.5
+// shares, 81 / 85 at 0.5 / 0.3), and at least one tile for each of 16 waves.
+int64_t item_tiles(int64_t total, int64_t cus) {
+  return std::max<int64_t>(16, total * 5 / (4 * cus) + 1);
+}
+
+// Whether a decode call runs with a workgroup per item (decode_item.h) rather
+// than split workgroups and a merge, given the items' 64-slot tiles.  The
+// lesser of two estimates in us, fitted to both sides measured at head_dim x
+// group 64 x 4, 128 x 4, 128 x 8 and 256 x 6, bf16 and fp8, 2 to 512 items of 128
+// to 8,192 slots:
+//   split: a launch pair of about 9 us and more (the q rows) for every 64 items,
+//     and the bytes at 6.2 TB/s;
+//   item: one launch whose workgroups take about 7.5 us and more each, one per
+//     CU at a time, and 15.5 us per million (slot x channel x q head) a CU
+//     multiplies; or the bytes at 5.2 TB/s where they bind; and a merge of
+//     4.5 us where items are split.
+// Split where items are few and long (8 items of 2,048 slots, 128 x 4: 11.7 us
+// against 26.8), by item where there are many (512 of 2,048 slots: 95 against
+// 166; 256 of 512: 20 against 55; 2 of 128, 64 x 4: 8.7 against 10.0).
+bool decode_by_item(const hwkv_cache *c, const std::vector<int64_t> &tiles) {
+  const double dg = (double)c->pol.head_dim * (double)group_size(c->pol);
+  const int64_t cus = hwkv::device_cu_count();
+  int64_t longest = 0, total = 0;
+  for (int64_t x : tiles) {
+    longest = std::max(longest, x);
+    total += x;
+  }
+  const double slots = 64.0, bytes = slots * (double)total * c->pol.head_dim * 2 * c->elem;
+  const double items = (double)tiles.size();
+  const double groups = std::ceil(items / hwkv::kMaxItems), rounds = std::ceil(items / (double)cus);
+  const double split = groups * (9.0 + 0.0025 * dg) + bytes / 6.2e6;
+  const int64_t T = item_tiles(total, cus);
+  const double base = 7.5 + 0.003 * dg + (c->fmt == HWKV_KV_FP8_E4M3 ? 2.8 : 0.0);
+  const double work = 15.5e-6 * dg * slots *
+                      std::max((double)std::min(longest, T), (double)total / (double)cus);
+  const double item = std::max(base * rounds + work, base + bytes / 5.2e6) + (longest > T ? 4.5 : 0.0);
+  return item < 0.95 * split;
+}
+
+// The launches of decode_by_item: up to kItemSeqs sequences each, heads by
+// capacity and sequences by length, longest first.
+// ws: room for the partials of `parts` workgroups (as many as the split
+// kernels' launches would leave; items stay whole where that is too little).
+int launch_items(hwkv_cache *c, int32_t layer, const void *k_new, const void *v_new, const void *q,
+                 float scale, void *out, float *ws, int64_t parts, bool fused, hipStream_t s) {
+  const hwkv_policy &p = c->pol;
+  const int32_t H = p.n_kv_heads, B = c->batch;
+  const int64_t G = group_size(p), D = p.head_dim;
+  hwkv::ItemArgs a;
+  std::memset(&a, 0, sizeof a);
+  std::vector<int32_t> order(H);
+  for (int32_t h = 0; h < H; ++h) {
+    const int32_t u = layer * H + h;
+    hwkv::ItemHead &hd = a.head[h];
+    hd.k_off = c->k_off[u];
+    hd.v_off = c->v_off[u];
+    hd.cap = (int32_t)c->cap[u];
+    hd.cap_pad = (int32_t)c->cap_pad[u];
+    hd.window = (int32_t)c->window[u];
+    hd.k_scale = c->k_scale[u];
+    hd.v_scale = c->v_scale[u];
+    order[h] = h;
+  }
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int32_t x, int32_t y) { return a.head[x].cap > a.head[y].cap; });
+  for (int32_t h = 0; h < H; ++h) a.head_order[h] = (uint8_t)order[h];
+  a.cache = c->base;
+  a.page_table = device_page_table(c);
+  a.pool_off = c->pool_off;
+  a.n_kv_heads = H;
+  a.n_sinks = p.n_sinks;
+  a.max_pages = (int32_t)c->max_pages;
+  a.scale_log2 = scale * 1.4426950408889634f;
+  for (int32_t b0 = 0; b0 < B; b0 += hwkv::kItemSeqs) {
+    const int32_t nb = std::min(hwkv::kItemSeqs, B - b0);
+    std::vector<int32_t> seqs(nb);
+    for (int32_t i = 0; i < nb; ++i) seqs[i] = b0 + i;
+    std::stable_sort(seqs.begin(), seqs.end(), [&](int32_t x, int32_t y) {
+      return seq_len(c, layer, x) > seq_len(c, layer, y);
+    });
+    for (int32_t i = 0; i < nb; ++i) {
+      a.seq[i] = (uint8_t)(seqs[i] - b0);
+      a.len[i] = (int32_t)(seq_len(c, layer, seqs[i]) + (fused ? 1 : 0));
+    }
+    a.n_seqs = nb;
+    // Split long items: tiles per workgroup and the workgroups that gives per
+    // run of sequences (heads in order, splits of the head's longest item)
+    int64_t total = 0, longest = 1;
+    for (int32_t h = 0; h < H; ++h)
+      for (int32_t i = 0; i < nb; ++i) {
+        const int64_t t = tiles_for(std::min(a.len[i], a.head[h].cap));
+        total += t;
+        longest = std::max(longest, t);
+      }
+    const int64_t cus = hwkv::device_cu_count();
+    int64_t T = item_tiles(total, cus);
+    auto begin = [&](int64_t per) {
+      int64_t runs = 0;
+      for (int32_t r = 0; r < H; ++r) {
+        a.wg_begin[r] = (uint16_t)runs;
+        runs += (tiles_for(std::min(a.len[0], a.head[order[r]].cap)) + per - 1) / per;
+      }
+      return runs;
+    };
+    if (longest <= T + T / 4 || begin(T) * nb > parts || begin(T) > UINT16_MAX) T = longest;
+    const int64_t runs = begin(T);
+    a.wg_begin[H] = (uint16_t)runs;
+    for (int32_t r = H + 1; r <= hwkv::kMaxItems; ++r) a.wg_begin[r] = UINT16_MAX;
+    a.tiles_per_wg = (int32_t)T;
+    a.part_acc = ws;
+    a.part_ml = ws ? ws + runs * nb * G * D : nullptr;
+    const bool merge = T < longest;
+    // everything the kernel finds by sequence starts at sequence b0
+    for (int32_t h = 0; h < H; ++h) {
+      const int32_t u = layer * H + h;
+      const int64_t at = (int64_t)b0 * c->cap_pad[u] * D;
+      a.head[h].k_off = c->k_off[u] + at;
+      a.head[h].v_off = c->v_off[u] + at;
+      a.head[h].page0 = page_tab_off(c, u, b0);
+    }
+    const size_t kv = (size_t)b0 * H * D, qo = kv * G;
+    a.q = static_cast<const uint16_t *>(q) + qo;
+    a.k_new = fused ? static_cast<const uint16_t *>(k_new) + kv : nullptr;
+    a.v_new = fused ? static_cast<const uint16_t *>(v_new) + kv : nullptr;
+    a.out = static_cast<float *>(out) + qo;
+    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
+    for (int e = 0; c->timing && e < 4; ++e) {
+      const int rc = next_event(c, &ev[e]);
+      if (rc != HWKV_OK) return rc;
+    }
+    if (c->timing) c->ev_merged.push_back(merge);
+    int rc = check_device(
+        hwkv::launch_decode_item(c->fmt, (int)D, (int)G, a, s, ev[0], ev[1]), "decode item launch");
+    if (rc == HWKV_OK && merge)
+      rc = check_device(hwkv::launch_item_merge((int)D, (int)G, a, s, ev[2], ev[3]),
+                        "decode item merge launch");
+    if (rc != HWKV_OK) return rc;
+  }
+  return HWKV_OK;
+}
+
 // Shared validation of a decode call; fills per-item lengths.  static_ws:
 // ws is the static scratch (an over-size call is refused with its limit).
 int decode_impl(hwkv_cache *c, int32_t layer, const void *k_new,
@@ -825,6 +970,14 @@ int decode_impl(hwkv_cache *c, int32_t layer, const void *k_new,
     const int rc = take_pages(c, layer, want, s);
     if (rc != HWKV_OK) return rc;
   }
+  if (decode_by_item(c, tiles)) {
+    const int rc = launch_items(c, layer, k_new, v_new, q, scale, out, static_cast<float *>(ws),
+                                total_splits, fused, s);
+    if (rc != HWKV_OK) return rc;
+    if (fused)
+      for (int32_t b = 0; b < B; ++b) seq_len(c, layer, b) += 1;
+    return ok();
+  }
   // launches of at most kMaxItems items
   int ws_split = 0;
   for (int i0 = 0; i0 < n_items_total; i0 += hwkv::kMaxItems) {
@@ -873,6 +1026,7 @@ int decode_impl(hwkv_cache *c, int32_t layer, const void *k_new,
     int rc;
     for (int e = 0; c->timing && e < 4; ++e)
       if ((rc = next_event(c, &ev[e])) != HWKV_OK) return rc;
+    if (c->timing) c->ev_merged.push_back(1);
     rc = check_device(
         hwkv::launch_decode_split(c->fmt, p.head_dim, G, a, splits, s, ev[0], ev[1]),
         "decode split launch");
@@ -1995,8 +2149,9 @@ int hwkv_decode_timing_read(hwkv_cache *c, double *split_ms, double *merge_ms,
   double sp = 0.0, mg = 0.0;
   const size_t n = c->ev_used / 4;
   if (n > 0) {
-    int rc = check_device(hipEventSynchronize(c->ev_pool[c->ev_used - 1]),
-                          "hipEventSynchronize");
+    int rc = check_device(
+        hipEventSynchronize(c->ev_pool[c->ev_used - (c->ev_merged[n - 1] ? 1 : 3)]),
+        "hipEventSynchronize");
     if (rc != HWKV_OK) return rc;
     for (size_t i = 0; i < n; ++i) {
       float t0 = 0.f, t1 = 0.f;
@@ -2004,9 +2159,10 @@ int hwkv_decode_timing_read(hwkv_cache *c, double *split_ms, double *merge_ms,
                                             c->ev_pool[4 * i + 1]),
                         "hipEventElapsedTime");
       if (rc != HWKV_OK) return rc;
-      rc = check_device(hipEventElapsedTime(&t1, c->ev_pool[4 * i + 2],
-                                            c->ev_pool[4 * i + 3]),
-                        "hipEventElapsedTime");
+      if (c->ev_merged[i])
+        rc = check_device(hipEventElapsedTime(&t1, c->ev_pool[4 * i + 2],
+                                              c->ev_pool[4 * i + 3]),
+                          "hipEventElapsedTime");
       if (rc != HWKV_OK) return rc;
       sp += t0;
       mg += t1;
@@ -2016,6 +2172,7 @@ int hwkv_decode_timing_read(hwkv_cache *c, double *split_ms, double *merge_ms,
   *merge_ms = mg;
   *launches = (int64_t)n;
   c->ev_used = 0;
+  c->ev_merged.clear();
   return ok();
 }
 

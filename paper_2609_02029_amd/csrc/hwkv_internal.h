@@ -75,6 +75,40 @@ struct DecodeArgs {
   float scale_log2;              // scale * log2(e)
 };
 
+// Decode of one launch with a workgroup per (sequence, kv head) item: the
+// layer's kv heads, and up to kItemSeqs of its sequences.
+constexpr int kItemSeqs = 192;
+struct ItemHead {
+  int64_t k_off, v_off;          // element offsets of the unit, sequence 0
+  int32_t cap, cap_pad;          // rows holding data; rows allocated
+  int32_t window;                // 0 = full
+  int32_t page0;                 // page-table offset of sequence 0, or -1
+  float k_scale, v_scale;        // fp8 scales of the unit (else 1)
+};
+struct ItemArgs {
+  ItemHead head[kMaxItems];
+  int32_t len[kItemSeqs];        // length, the appended token included
+  uint8_t seq[kItemSeqs];        // its sequence, from seq0 on
+  uint8_t head_order[kMaxItems];
+  void *cache;
+  const uint16_t *q;             // as in DecodeArgs
+  const uint16_t *k_new;         // null: nothing is appended
+  const uint16_t *v_new;
+  float *out;
+  const int32_t *page_table;     // paged caches (else null)
+  int64_t pool_off;
+  int32_t n_seqs, n_kv_heads, n_sinks, max_pages;
+  float scale_log2;
+  // Split items: the r-th head of head_order has wg_begin[r + 1] - wg_begin[r]
+  // = splits x n_seqs workgroups, split by split; split j of an item takes its
+  // tiles [j T, (j + 1) T), T = tiles_per_wg, and an item of more than T tiles
+  // leaves one partial per split for item_merge (acc part_acc[workgroup][G][D],
+  // (m, l) part_ml[workgroup][G][2]).
+  int32_t tiles_per_wg;
+  uint16_t wg_begin[kMaxItems + 1];   // in units of n_seqs workgroups
+  float *part_acc, *part_ml;
+};
+
 // Materialisation of one chunk: for kv head h, the tiles listed in up to
 // three disjoint ranges [tile0[r], tile0[r] + n_tiles[r]).
 struct WriteHead {
@@ -195,6 +229,13 @@ template <int F>
 hipError_t launch_decode_split_fmt(int D, int G, const DecodeArgs &a,
                                    int n_splits, hipStream_t s, hipEvent_t e0,
                                    hipEvent_t e1);
+hipError_t launch_decode_item(int fmt, int D, int G, const ItemArgs &a, hipStream_t s,
+                              hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+hipError_t launch_item_merge(int D, int G, const ItemArgs &a, hipStream_t s,
+                             hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+template <int F>
+hipError_t launch_decode_item_fmt(int D, int G, const ItemArgs &a, hipStream_t s, hipEvent_t e0,
+                                  hipEvent_t e1);
 hipError_t launch_decode_combine(int D, int G, const DecodeArgs &a,
                                  int n_combine_blocks, hipStream_t s,
                                  hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
@@ -308,6 +349,7 @@ hipError_t launch_calib_means(const CalibArgs &a, hipStream_t s);
 
 // Kernel arguments travel by value; the kernarg segment is limited to 4 KiB.
 static_assert(sizeof(hwkv::DecodeArgs) <= 4096, "decode kernarg too large");
+static_assert(sizeof(hwkv::ItemArgs) <= 4096, "decode item kernarg too large");
 static_assert(sizeof(hwkv::WriteArgs) <= 4096, "write kernarg too large");
 static_assert(sizeof(hwkv::AppendArgs) <= 4096, "append kernarg too large");
 static_assert(sizeof(hwkv::PageUpdateArgs) <= 4096, "page update kernarg too large");
