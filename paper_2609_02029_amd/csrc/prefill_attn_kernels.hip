@@ -68,8 +68,8 @@
 //           touches four 64-byte pieces that the odd-row swizzle and the pair
 //           pad place on disjoint banks of the 256-byte-wide LDS.
 // Every operand address is a per-lane base plus a compile-time offset.
-// Keys past the tile's range read a zero row, so they are exact zeros (and
-// masked).
+// Keys past the tile's range lie past the buffer's span, so they read as zeros
+// (and are masked).
 //
 // Binary16 caches (prefill_attn<.., true>): the same tiles, loads and
 // layouts (both formats are 2-byte elements), on v_mfma_f32_32x32x16_f16.
@@ -92,9 +92,6 @@
 #include "hwkv_internal.h"
 
 namespace hwkv {
-
-// A zero row (head_dim <= 256): the source of every key past a tile's range
-__device__ __attribute__((aligned(16))) uint32_t g_zero_row[128] = {};
 
 namespace {
 
@@ -137,13 +134,8 @@ __device__ __forceinline__ f32x16_t mfma16(u32x4_t a, u32x4_t b, f32x16_t c) {
                                                    __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// 16 bytes from global memory into the LDS block of the issuing instruction
-__device__ __forceinline__ void g2lds(const void *src, uint8_t *lds_block) {
-  __builtin_amdgcn_global_load_lds(src, (lds_void_t *)lds_block, 16, 0, 0);
-}
-
-// The same at a scalar base and 32-bit byte offsets (lane's and uniform).  The
-// descriptor spans 2^31 bytes (a unit's K or V is smaller); an access is out
+// 16 bytes from global memory into the LDS block of the issuing instruction, at
+// a scalar base and 32-bit byte offsets (lane's and uniform).  The descriptor spans 2^31 bytes (a unit's K or V is smaller); an access is out
 // of range, and reads as zero, where the lane's offset is at or past the span
 // less the uniform offset, so a lane offset of the span itself always is.
 constexpr uint32_t kSpan = 0x80000000u;
@@ -215,6 +207,111 @@ struct Prefill {
   static constexpr int STAGE = KBYTES + VBYTES;
   static constexpr int IPW = (NINST + NW - 1) / NW;   // per wave and tile, each of K, V
 };
+
+// The V^T operand of 16-key step s of a block at 32-channel block db (vl: the
+// block's V with the lane's offset).
+template <typename P>
+__device__ __forceinline__ u32x4_t read_values(const uint8_t *vl, int s, int db) {
+  i16x4_t v2[2];
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh)
+    v2[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (lds_i16x4_t *)(vl + 2 * db * P::VPAIR + (16 * s + 8 * hh) * 16));
+  return __builtin_bit_cast(u32x4_t,
+                            __builtin_shufflevector(v2[0], v2[1], 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// The products of a phase: S^T of a tile of U blocks of 32 keys (K at kl) and,
+// if VALUES, O^T += V^T P^T of the one before it (V at vl; 16 keys a step, two
+// steps a block).  They alternate, and so do the blocks of S^T: a product that
+// adds to the one before it would wait out that one's latency.  The order of
+// operand reads and products is pinned, reads kPipe products of their kind
+// ahead: left to itself the scheduler reads each operand just before its
+// product and waits out the LDS latency every time.
+template <int D, int NW, bool F16, int U, bool VALUES>
+__device__ __forceinline__ void tile_products(f32x16_t (&o)[D / 32], f32x16_t (&st)[U],
+                                              const u32x4_t (&pb)[2 * U], const u32x4_t (&qv)[D / 16],
+                                              const uint8_t *kl, const uint8_t *vl) {
+  using P = Prefill<D, NW>;
+  constexpr int KS = P::KS, DB = P::DB;
+  constexpr int N = U * KS;                      // products of each kind
+  static_assert(N == 2 * U * DB, "as many products of both kinds");
+  constexpr int A = VALUES ? kPipe : 2 * kPipe;
+  u32x4_t kx[A], va[A];
+  auto read_k = [&](int i) {
+    kx[i % A] = *reinterpret_cast<const u32x4_t *>(kl + (i % U) * P::STAGE + (i / U) * 1024);
+  };
+  auto read_v = [&](int i) {
+    const int s = i / DB, db = i % DB;
+    va[i % A] = read_values<P>(vl + (s / 2) * P::STAGE, s % 2, db);
+  };
+#pragma unroll
+  for (int i = 0; i < A; ++i) {
+    read_k(i);
+    if constexpr (VALUES) read_v(i);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i < U)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st[i % U][r] = 0.0f;
+    pin();
+    st[i % U] = mfma16<F16>(kx[i % A], qv[i / U], st[i % U]);
+    pin();
+    if (i + A < N) read_k(i + A);
+    if constexpr (VALUES) {
+      pin();
+      o[i % DB] = mfma16<F16>(va[i % A], pb[i / DB], o[i % DB]);
+      pin();
+      if (i + A < N) read_v(i + A);
+    }
+  }
+  pin();
+}
+
+// The weights 2^(st c2 - mc) of a tile, packed for the value product, and their
+// sum added to l.  Every weight comes before the sums and the packing, which
+// would otherwise each wait for its exponential.
+template <int U, bool F16>
+__device__ __forceinline__ void tile_weights(f32x16_t (&st)[U], u32x4_t (&pb)[2 * U], float &l,
+                                             float c2, float mc) {
+#pragma unroll
+  for (int r = 0; r < 16 * U; ++r)
+    st[r / 16][r % 16] = __builtin_fmaf(st[r / 16][r % 16], c2, -mc);
+  pin();
+#pragma unroll
+  for (int r = 0; r < 16 * U; ++r) st[r / 16][r % 16] = __builtin_amdgcn_exp2f(st[r / 16][r % 16]);
+  pin();
+  float ls[4] = {l, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int r = 0; r < 16 * U; r += 2) {
+    const float w0 = st[r / 16][r % 16], w1 = st[r / 16][r % 16 + 1];
+    ls[r % 4] += w0;
+    ls[r % 4 + 1] += w1;
+    pb[r / 8][r % 8 / 2] = F16 ? pack_f16(w0, w1) : pack_bf16(w0, w1);
+  }
+  l = (ls[0] + ls[1]) + (ls[2] + ls[3]);
+}
+
+// The largest of a tile's logits, in both lanes of a column.
+template <int U>
+__device__ __forceinline__ float tile_max(const f32x16_t (&st)[U]) {
+  float mx = max_of(st[0][0], st[0][1]), lo, hi;
+#pragma unroll
+  for (int r = 2; r < 16 * U; r += 2)
+    mx = max_of(max_of(mx, st[r / 16][r % 16]), st[r / 16][r % 16 + 1]);
+  halves(mx, &lo, &hi);
+  return max_of(lo, hi);
+}
+
+// Every wave's LDS reads are done, and the loads it waited for are in LDS.
+__device__ __forceinline__ void phase_end() {
+  asm volatile("" ::: "memory");
+  pin();
+  __builtin_amdgcn_s_barrier();
+  pin();
+  asm volatile("" ::: "memory");
+}
 
 template <int D, int NW, bool F16>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
@@ -506,12 +603,9 @@ void prefill_attn(const PrefillAttnArgs a) {
       }
     }
   };
-  // raises the shift (and rescales the sums) where a block's maximum mx of
-  // this lane half exceeds it by more than 8 in base 2
+  // raises the shift (and rescales the sums) where a tile's maximum exceeds it
+  // by more than 8 in base 2
   auto raise = [&](float mx) {
-    float lo_half, hi_half;
-    halves(mx, &lo_half, &hi_half);
-    mx = max_of(lo_half, hi_half);
     if (__any(mx > m + tau)) {
       const float mn = fmaxf(m, mx);
       const float alpha = __builtin_amdgcn_exp2f((m - mn) * c2);
@@ -523,56 +617,9 @@ void prefill_attn(const PrefillAttnArgs a) {
         for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
     }
   };
-  // The products of a phase: S^T of a tile (K at kl) and, if VALUES, O^T +=
-  // V^T P^T of the one before it (V at vl; 16 keys a step, two steps a block).
-  // They alternate, and so do the two blocks of S^T: a product that
-  // adds to the one before it would wait out that one's latency.  The order
-  // of operand reads and products is pinned, reads kPipe products of their
-  // kind ahead: left to itself the scheduler reads each operand just before
-  // its product and waits out the LDS latency every time.
-  constexpr int N = U * KS;                      // products of each kind
-  static_assert(N == 2 * U * DB, "as many products of both kinds");
-  auto products = [&](auto values, f32x16_t (&st)[U], const u32x4_t (&pb)[2 * U],
-                      const uint8_t *kl, const uint8_t *vl) {
-    constexpr bool VALUES = decltype(values)::value;
-    constexpr int A = VALUES ? kPipe : 2 * kPipe;
-    u32x4_t kx[A], va[A];
-    auto read_k = [&](int i) {
-      kx[i % A] = *reinterpret_cast<const u32x4_t *>(kl + (i % U) * P::STAGE + (i / U) * 1024);
-    };
-    auto read_v = [&](int i) {
-      const int s = i / DB, db = i % DB;
-      i16x4_t v2[2];
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh)
-        v2[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (lds_i16x4_t *)(vl + (s / 2) * P::STAGE + 2 * db * P::VPAIR +
-                            (16 * (s % 2) + 8 * hh) * 16));
-      va[i % A] = __builtin_bit_cast(
-          u32x4_t, __builtin_shufflevector(v2[0], v2[1], 0, 1, 2, 3, 4, 5, 6, 7));
-    };
-#pragma unroll
-    for (int i = 0; i < A; ++i) {
-      read_k(i);
-      if constexpr (VALUES) read_v(i);
-    }
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      if (i < U)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st[i % U][r] = 0.0f;
-      pin();
-      st[i % U] = mfma16<F16>(kx[i % A], qv[i / U], st[i % U]);
-      pin();
-      if (i + A < N) read_k(i + A);
-      if constexpr (VALUES) {
-        pin();
-        o[i % DB] = mfma16<F16>(va[i % A], pb[i / DB], o[i % DB]);
-        pin();
-        if (i + A < N) read_v(i + A);
-      }
-    }
-    pin();
+  auto products = [&](auto values, f32x16_t (&st)[U], const u32x4_t (&pb)[2 * U], const uint8_t *kl,
+                      const uint8_t *vl) {
+    tile_products<D, NW, F16, U, decltype(values)::value>(o, st, pb, qv, kl, vl);
   };
   // Tiles [f0, f0 + fn) of this split are seen whole by every column of the
   // wave.
@@ -592,15 +639,6 @@ void prefill_attn(const PrefillAttnArgs a) {
     const int slast = min(s0 + KT, se) - 1;
     return wave_live && s0 <= t_hi && !(W != 0 && s0 >= S && slast < t_lo + 1 - W);
   };
-  // every wave's LDS reads are done and the loads it waited for are in LDS
-  auto phase_end = [&]() {
-    asm volatile("" ::: "memory");
-    pin();
-    __builtin_amdgcn_s_barrier();
-    pin();
-    asm volatile("" ::: "memory");
-  };
-
   // q has arrived before the loop: a wait for it inside would wait for the
   // tiles' loads too
 #pragma unroll
@@ -640,31 +678,8 @@ void prefill_attn(const PrefillAttnArgs a) {
 #pragma unroll
         for (int u = 0; u < U; ++u) mask(st[u], s0 + kKeys * u, se);
       }
-      float mx = max_of(st[0][0], st[0][1]);
-#pragma unroll
-      for (int r = 2; r < 16 * U; r += 2)
-        mx = max_of(max_of(mx, st[r / 16][r % 16]), st[r / 16][r % 16 + 1]);
-      raise(mx);
-      // every weight before the sums and the packing, which would otherwise
-      // each wait for its exponential
-      const float mc = m * c2 - pbias;
-#pragma unroll
-      for (int r = 0; r < 16 * U; ++r)
-        st[r / 16][r % 16] = __builtin_fmaf(st[r / 16][r % 16], c2, -mc);
-      pin();
-#pragma unroll
-      for (int r = 0; r < 16 * U; ++r)
-        st[r / 16][r % 16] = __builtin_amdgcn_exp2f(st[r / 16][r % 16]);
-      pin();
-      float ls[4] = {l, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int r = 0; r < 16 * U; r += 2) {
-        const float w0 = st[r / 16][r % 16], w1 = st[r / 16][r % 16 + 1];
-        ls[r % 4] += w0;
-        ls[r % 4 + 1] += w1;
-        pb[r / 8][r % 8 / 2] = F16 ? pack_f16(w0, w1) : pack_bf16(w0, w1);
-      }
-      l = (ls[0] + ls[1]) + (ls[2] + ls[3]);
+      raise(tile_max(st));
+      tile_weights<U, F16>(st, pb, l, c2, m * c2 - pbias);
     }
     so1 = so;
     so = so == (STAGES - 1) * SB ? 0 : so + SB;
@@ -780,24 +795,26 @@ __global__ __launch_bounds__(256) void prefill_merge(const PrefillAttnArgs a) {
       make_float4(A.x * inv, A.y * inv, A.z * inv, A.w * inv);
 }
 
-// Calibration replay in one pass.  Workgroups and columns as in prefill_attn
-// (column c = row * G + g of one KV head, row r at position rows[r]); the
-// keys are the traced history, each candidate window w holds the sinks
-// [0, S) and the suffix [max(S, t + 1 - w), t] of row position t, and the
-// full candidate holds every s <= t.  The suffixes are nested, so a column
-// walks its keys once, from the top tile down: when the walk has added every
-// key at or above a window's edge t + 1 - w, the running (m, l, acc) is that
-// window's share of the split, written out there.  A tile holding an edge is
-// added in up to two passes of the V^T P^T product per edge: the keys at or
-// above the edge, then the rest.  Split y < n_splits covers key tiles
-// [y tps, (y + 1) tps) of [0, t_last] without the sinks; split n_splits adds
-// the sinks alone.  replay_merge assembles each candidate.
+// Calibration replay in one pass.  Workgroups, columns and phases as in
+// prefill_attn (column c = row * G + g of one KV head, row r at position
+// rows[r]; tiles of 32 keys); the keys are the traced history, each candidate
+// window w holds the sinks [0, S) and the suffix [max(S, t + 1 - w), t] of row
+// position t, and the full candidate holds every s <= t.  The suffixes are
+// nested, so a column walks its keys once, from the top tile down: when the walk
+// has added every key at or above a window's edge t + 1 - w, the running
+// (m, l, acc) is that window's share of the split, written out there.  A tile
+// holding an edge is added on its own, in the softmax phase, in up to two
+// passes of the V^T P^T product per edge: the keys at or above the edge, then
+// the rest.  Split y < n_splits covers key tiles [y tps, (y + 1) tps) of
+// [0, t_last] without the sinks; split n_splits adds the sinks alone.
+// replay_merge assembles each candidate.
 template <int D, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void replay_attn(const ReplayAttnArgs a) {
   using P = Prefill<D, NW>;
   constexpr int KS = P::KS, DB = P::DB;
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * P::STAGE];
+  constexpr int STAGES = 4;
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[STAGES * P::STAGE];
   __shared__ int swin[kMaxWindows];
 
   const int nb = a.n_col_blocks;
@@ -821,21 +838,16 @@ void replay_attn(const ReplayAttnArgs a) {
   const bool wave_live = wc0 <= c_last;
   const int wc_last = min(wc0 + 31, c_last);
   const int t_lo = rows[min(wc0, c_last) / G], t_hi = rows[wc_last / G];
-  const int c = wc0 + cl;
-  const bool col_ok = c <= c_last;
-  const int cc = min(c, c_last);
-  const int tl = cc / G, g = cc - tl * G;
-  const int t = rows[tl];
-  const size_t q_row = ((size_t)tl * Hq + (size_t)h * G + g) * D;
   const size_t n_cols = (size_t)a.n_rows * Hq;
-  // the lane's column id (row * Hq + h * G + g), recomputed where it is
-  // needed rather than kept live through the tile loop
+  // the lane's column (the last one where it has none) and its id (row * Hq +
+  // h * G + g), recomputed where they are needed rather than kept live
+  // through the tile loop
+  auto column = [&]() { return min(wc0 + (lane_now() & 31), c_last); };
   auto column_id = [&]() -> size_t {
-    int cx = wc0 + (int)(threadIdx.x & 31);
-    asm volatile("" : "+v"(cx));
-    const int ccx = min(cx, c_last), tx = ccx / G;
+    const int ccx = column(), tx = ccx / G;
     return (size_t)tx * Hq + (size_t)h * G + (size_t)(ccx - tx * G);
   };
+  const int t = rows[column() / G];
 
   // this workgroup's key tiles
   const int ntiles = tb / kKeys + 1;
@@ -849,8 +861,8 @@ void replay_attn(const ReplayAttnArgs a) {
     i_hi = min(ntiles, i_lo + a.tiles_per_split);
   }
   if (i_lo >= i_hi) {                               // uniform: an empty split
-    if (col_ok && half == 0) {
-      float *pp = a.part + ((size_t)blockIdx.y * n_cols + q_row / D) * (D + 4);
+    if (wc0 + cl <= c_last && half == 0) {
+      float *pp = a.part + ((size_t)blockIdx.y * n_cols + column_id()) * (D + 4);
       pp[0] = -1e30f;
       pp[1] = 0.0f;
     }
@@ -859,30 +871,32 @@ void replay_attn(const ReplayAttnArgs a) {
   for (int i = tid; i < K; i += NW * 64) swin[i] = a.windows[i];
 
   u32x4_t qv[KS];
+  {
+    const uint16_t *qr = a.q + column_id() * D + 8 * half;
+    const bool ok = wc0 + cl <= c_last;
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
-    qv[ks] = col_ok ? ld16(a.q + q_row + 16 * ks + 8 * half) : u32x4_t{0, 0, 0, 0};
+    for (int ks = 0; ks < KS; ++ks) qv[ks] = ok ? ld16(qr + 16 * ks) : u32x4_t{0, 0, 0, 0};
+  }
 
+  // Tile loads: chunk rows 2n, 2n + 1 by wave n % NW (see prefill_attn), from
+  // the top tile down; keys past the block's last position read as zeros.
   const size_t in_stride = (size_t)a.n_kv_heads * D;
-  const uint16_t *kin = a.k + (size_t)h * D;
-  const uint16_t *vin = a.v + (size_t)h * D;
-  const uint16_t *zero = reinterpret_cast<const uint16_t *>(g_zero_row);
-  // the key this lane loads in every tile (see prefill_attn)
-  const int lkey = cl ^ (4 * half);
-  auto issue_loads = [&](int i, int buf) {
-    const int s = i * kKeys + lkey;
-    const uint16_t *kp = s <= tb ? kin + (size_t)s * in_stride : zero;
-    const uint16_t *vp = s <= tb ? vin + (size_t)s * in_stride : zero;
-    uint8_t *kl = smem + buf * P::STAGE;
-    uint8_t *vl = kl + P::KBYTES;
+  const int n_it = i_hi - i_lo;
+  const uint8_t *run_k = scalar_ptr(a.k + (size_t)(i_hi - 1) * kKeys * in_stride + (size_t)h * D);
+  const uint8_t *run_v = scalar_ptr(a.v + (size_t)(i_hi - 1) * kKeys * in_stride + (size_t)h * D);
+  const int tile_bytes = kKeys * (int)in_stride * 2;
+  int vo = (cl ^ (4 * half)) * (int)in_stride * 2 + half * 16;
+  auto issue_loads = [&](uint8_t *stage, int off) {
+    const rsrc_t kr = make_rsrc(run_k), vr = make_rsrc(run_v);
 #pragma unroll
     for (int j = 0; j < P::IPW; ++j) {
       const int n = wave + j * NW;
       if (P::NINST % NW != 0 && n >= P::NINST) break;   // uniform per wave
-      const int ch = 2 * n + half;
-      g2lds(kp + ch * 8, kl + n * 1024);
-      g2lds(vp + ch * 8, vl + n * P::VPAIR);
+      b2lds(kr, stage + n * 1024, off, n * 32);
+      b2lds(vr, stage + P::KBYTES + n * P::VPAIR, off, n * 32);
     }
+    run_k = scalar_ptr(run_k - tile_bytes);
+    run_v = scalar_ptr(run_v - tile_bytes);
   };
 
   // logit scale, base 2, with the keys' scale; uniform (scalar register)
@@ -896,178 +910,164 @@ void replay_attn(const ReplayAttnArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
 
-  const int klane = half * 512 + lkey * 16;
+  int klane = half * 512 + (cl ^ (4 * half)) * 16;
   const int gq = lane >> 4, mq = lane & 15;
   const int vpar = (mq >> 1) & 1;
   const int vkey0 = 4 * (gq >> 1) + (mq >> 2);
-  const int vlane = (gq & 1) * P::VPAIR + vpar * 512 + (vkey0 ^ (4 * vpar)) * 16 + (mq & 1) * 8;
+  int vlane = P::KBYTES + (gq & 1) * P::VPAIR + vpar * 512 + (vkey0 ^ (4 * vpar)) * 16 +
+              (mq & 1) * 8;
+  asm volatile("" : "+v"(klane), "+v"(vlane), "+v"(vo));
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qv[ks]));
 
-  issue_loads(i_hi - 1, 0);
-  __syncthreads();                               // swin
+  {
+    const int s = (i_hi - 1) * kKeys + (cl ^ (4 * half));
+    issue_loads(smem, s <= tb ? vo : kNoRow);
+  }
+  if (n_it > 1) issue_loads(smem + P::STAGE, vo);
+  wait_loads();
+  __syncthreads();                               // swin too
   // The lane's next window: the first whose edge lies below this split's top
   // (windows with an edge at or above it have no key here).  An edge at or
   // below S means the window holds every key: it is the full candidate.
   const int top = i_hi * kKeys;
   int kn = 0;
   int edge = INT_MIN;
+  auto edge_of = [&](int k) {
+    return (k < K && t + 1 - swin[k] > S) ? t + 1 - swin[k] : INT_MIN;
+  };
   if (!sink_pass) {
     while (kn < K && t + 1 - swin[kn] >= top) ++kn;
-    edge = (kn < K && t + 1 - swin[kn] > S) ? t + 1 - swin[kn] : INT_MIN;
+    edge = edge_of(kn);
   }
+  phase_end();
+  const bool late = wave >= NW / 2;              // the second group
+  if (late) phase_end();
 
-  // V^T P^T over the keys of rows [lo, hi) of this lane's tile rows (key of
-  // row r: s0 + 4 half + 8 (r / 4) + r % 4), adding their weights to l
-  auto add_keys = [&](const float (&pr)[16], int s0, int lo, int hi, const uint8_t *vl) {
-    u32x4_t pb[2];
-    const int e = s0 + 4 * half;
-    float ls = 0.0f;
+  f32x16_t st[1];                                // S^T of the tile
+  u32x4_t pb[2];                                 // the weights of the tile, packed
+  bool held = false;                             // pb holds weights to add
+  int so = 0, so1 = 0;                           // LDS offsets of tiles it, it - 1
+  for (int it = 0;; ++it) {
+    // ---- products: S^T of tile it, then V^T P^T of tile it - 1
+    const int s0 = (i_hi - 1 - it) * kKeys;      // tiles from the top down
+    const bool vis = it < n_it && wave_live && s0 <= t_hi &&
+                     (sink_pass ? s0 < S : s0 + kKeys > S);
+    const uint8_t *kl = smem + so + klane, *vl = smem + so1 + vlane;
+    // One pass, or for a tile that holds window edges one per edge and the rest:
+    // first the keys at or above a lane's next edge (the whole tile where it
+    // has none), whose state is then the window's partial, then those below
+    // the last edge taken; the logits are formed again for each.  (One call of
+    // the products for all of them: a second place that adds to o would take
+    // a second set of its registers.)
+    bool act = false;                            // the lane's edge is in this pass
+    int lo = s0, cut = s0 + kKeys;               // its keys: [lo, cut)
+    for (bool first = true;; first = false) {
+      __builtin_amdgcn_s_waitcnt(0xc07f);        // as in prefill_attn
+      if (held)
+        tile_products<D, NW, false, 1, true>(o, st, pb, qv, kl, vl);
+      else if (vis)
+        tile_products<D, NW, false, 1, false>(o, st, pb, qv, kl, vl);
+      held = false;
+      if (first) {
+        wait_loads();                            // tile it + 1, issued a phase ago
+        if (it == n_it) break;
+        phase_end();
+        // ---- softmax of tile it
+        if (it + 2 < n_it)
+          issue_loads(smem + (so >= 2 * P::STAGE ? so - 2 * P::STAGE : so + 2 * P::STAGE), vo);
+        if (!vis) break;
+      } else {
+        // the windows' partials, for the lanes whose edge this pass reached
+        float l_lo, l_hi;
+        halves(l, &l_lo, &l_hi);
+        if (act && wc0 + (lane_now() & 31) <= c_last) {
+          const int hf = lane_now() >> 5;
+          const size_t col_id = column_id();
+          float *wa = a.win_acc + ((size_t)kn * n_cols + col_id) * D;
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+          for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r0 = 8 * s + 2 * j, r1 = r0 + 1;
-        const int k0 = e + (r0 >> 2) * 8 + (r0 & 3), k1 = e + (r1 >> 2) * 8 + (r1 & 3);
-        const float p0 = (k0 >= lo && k0 < hi) ? pr[r0] : 0.0f;
-        const float p1 = (k1 >= lo && k1 < hi) ? pr[r1] : 0.0f;
-        ls += p0 + p1;
-        pb[s][j] = pack_bf16(p0, p1);
+            for (int rq = 0; rq < 4; ++rq)
+              *reinterpret_cast<float4 *>(wa + 32 * db + 8 * rq + 4 * hf) =
+                  make_float4(o[db][4 * rq + 0], o[db][4 * rq + 1], o[db][4 * rq + 2],
+                              o[db][4 * rq + 3]);
+          if (hf == 0)
+            *reinterpret_cast<float2 *>(a.win_ml + ((size_t)kn * n_cols + col_id) * 2) =
+                make_float2(m, l_lo + l_hi);
+        }
+        if (act) {
+          ++kn;
+          edge = edge_of(kn);
+        }
+        cut = lo;
+        if (!__any(cut > s0)) break;
       }
-    l += ls;
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        i16x4_t v2[2];
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-          v2[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (lds_i16x4_t *)(vl + 2 * db * P::VPAIR + (16 * s + 8 * hh) * 16));
-        const bf16x8_t va = __builtin_bit_cast(
-            bf16x8_t, __builtin_shufflevector(v2[0], v2[1], 0, 1, 2, 3, 4, 5, 6, 7));
-        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            va, __builtin_bit_cast(bf16x8_t, pb[s]), o[db], 0, 0, 0);
-      }
-    }
-  };
-
-  const int n_it = i_hi - i_lo;
-  for (int it = 0; it < n_it; ++it) {
-    const int i = i_hi - 1 - it;                 // tiles from the top down
-    wait_loads();
-    __syncthreads();
-    if (it + 1 < n_it) issue_loads(i - 1, (it + 1) & 1);
-    const int s0 = i * kKeys;
-    const bool skip = !wave_live || s0 > t_hi ||
-                      (sink_pass ? s0 >= S : s0 + kKeys <= S);
-    if (skip) continue;
-    const uint8_t *kl = smem + (it & 1) * P::STAGE + klane;
-    const uint8_t *vl = smem + (it & 1) * P::STAGE + P::KBYTES + vlane;
-    // S^T of the tile, masked: visible keys are s <= t, and s < S in the
-    // sink pass, s >= S otherwise
-    const bool full_vis = s0 + kKeys - 1 <= t_lo && (sink_pass ? s0 + kKeys <= S : s0 >= S);
-    auto logits = [&]() -> f32x16_t {
-      f32x16_t st;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) st[r] = 0.0f;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const u32x4_t kx = *reinterpret_cast<const u32x4_t *>(kl + ks * 1024);
-        st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            __builtin_bit_cast(bf16x8_t, kx), __builtin_bit_cast(bf16x8_t, qv[ks]), st, 0, 0, 0);
-      }
-      if (!full_vis) {
-        int e = s0 + 4 * half, d = e - t;
+      // visible keys: s <= t, and s < S in the sink pass, s >= S otherwise
+      if (!(s0 + kKeys - 1 <= t_lo && (sink_pass ? s0 + kKeys <= S : s0 >= S))) {
+        int e = s0 + 4 * (lane_now() >> 5), d = e - t;
         asm volatile("" : "+v"(e), "+v"(d));
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int cr = (r >> 2) * 8 + (r & 3);
-          const bool vis = (d <= -cr) & (sink_pass ? (e < S - cr) : (e >= S - cr));
-          if (!vis) st[r] = -__builtin_inff();
+          const bool seen = (d <= -cr) & (sink_pass ? (e < S - cr) : (e >= S - cr));
+          if (!seen) st[0][r] = -__builtin_inff();
         }
       }
-      return st;
-    };
-    // a window's partial at its edge, for the lanes whose edge lies in this
-    // tile; those lanes move to their next window
-    auto edge_partials = [&](bool act) {
-      float l_lo, l_hi;
-      halves(l, &l_lo, &l_hi);
-      if (act && wc0 + cl <= c_last) {
-        const size_t col_id = column_id();
-        float *wa = a.win_acc + ((size_t)kn * n_cols + col_id) * D;
+      if (first) {
+        const float mx = tile_max(st);
+        if (__any((mx - m) * c2 > 8.0f)) {       // lazy rescale: shift moves by > 8
+          const float mn = fmaxf(m, mx);
+          const float alpha = __builtin_amdgcn_exp2f((m - mn) * c2);
+          m = mn;
+          l *= alpha;
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+          for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int rq = 0; rq < 4; ++rq)
-            *reinterpret_cast<float4 *>(wa + 32 * db + 8 * rq + 4 * half) =
-                make_float4(o[db][4 * rq + 0], o[db][4 * rq + 1], o[db][4 * rq + 2],
-                            o[db][4 * rq + 3]);
-        if (half == 0)
-          *reinterpret_cast<float2 *>(a.win_ml + ((size_t)kn * n_cols + col_id) * 2) =
-              make_float2(m, l_lo + l_hi);
+            for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+        }
       }
-      if (act) {
-        ++kn;
-        edge = (kn < K && t + 1 - swin[kn] > S) ? t + 1 - swin[kn] : INT_MIN;
+      held = true;                               // added with the next products
+      act = edge >= s0;
+      const bool edges = __any(act);             // uniform; rare
+      if (first && !edges) {
+        tile_weights<1, false>(st, pb, l, c2, m * c2);
+        break;
       }
-    };
-
-    float mc;
-    {
-      const f32x16_t st = logits();
-      float mx = st[0];
+      lo = act ? edge : s0;
+      const float mc = m * c2;
+      const int e = s0 + 4 * (lane_now() >> 5);
+      float ls = 0.0f;
 #pragma unroll
-      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, st[r]);
-      {
-        float lo_half, hi_half;
-        halves(mx, &lo_half, &hi_half);
-        mx = fmaxf(lo_half, hi_half);
-      }
-      if (__any((mx - m) * c2 > 8.0f)) {        // lazy rescale: shift moves by > 8
-        const float mn = fmaxf(m, mx);
-        const float alpha = __builtin_amdgcn_exp2f((m - mn) * c2);
-        m = mn;
-        l *= alpha;
+      for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-      }
-      mc = m * c2;
-      float pr[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) pr[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[r], c2, -mc));
-      // First pass: a lane whose next window edge lies in this tile adds the
-      // keys at or above the edge; every other lane adds the whole tile.
-      const bool act = edge >= s0;
-      add_keys(pr, s0, act ? edge : s0, s0 + kKeys, vl);
+        for (int j = 0; j < 4; ++j) {
+          const int r0 = 8 * s + 2 * j, r1 = r0 + 1;
+          const int k0 = e + (r0 >> 2) * 8 + (r0 & 3), k1 = e + (r1 >> 2) * 8 + (r1 & 3);
+          const float w0 = __builtin_amdgcn_exp2f(__builtin_fmaf(st[0][r0], c2, -mc));
+          const float w1 = __builtin_amdgcn_exp2f(__builtin_fmaf(st[0][r1], c2, -mc));
+          const float p0 = (k0 >= lo && k0 < cut) ? w0 : 0.0f;
+          const float p1 = (k1 >= lo && k1 < cut) ? w1 : 0.0f;
+          ls += p0 + p1;
+          pb[s][j] = pack_bf16(p0, p1);
+        }
+      l += ls;
+      if (!edges) break;
+      vl = smem + so + vlane;                    // this tile's values, now
     }
-    if (__any(edge >= s0)) {                     // uniform; rare
-      // Further passes, each over the keys below the last edge taken: the
-      // logits and weights are recomputed from the tile (same shift, same
-      // values) rather than kept live through the passes.
-      bool act = edge >= s0;                     // the lanes of the first pass
-      int cut = act ? edge : s0;                 // keys [s0, cut) not added yet
-      while (true) {
-        edge_partials(act);
-        if (!__any(cut > s0)) break;
-        act = edge >= s0;                        // the lane's next edge, below cut
-        const int lo = act ? edge : s0;
-        const f32x16_t st = logits();
-        float pr[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) pr[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[r], c2, -mc));
-        add_keys(pr, s0, lo, cut, vl);
-        cut = lo;
-      }
-    }
+    if (it == n_it) break;
+    so1 = so;
+    so = so == (STAGES - 1) * P::STAGE ? 0 : so + P::STAGE;
+    phase_end();
   }
+  if (!late) phase_end();
 
   float l_lo, l_hi;
   halves(l, &l_lo, &l_hi);
-  if (wc0 + cl > c_last) return;
+  if (wc0 + (lane_now() & 31) > c_last) return;
+  const int hf = lane_now() >> 5;
   float *pp = a.part + ((size_t)blockIdx.y * n_cols + column_id()) * (D + 4);
-  if (half == 0) {
+  if (hf == 0) {
     pp[0] = m;
     pp[1] = l_lo + l_hi;
   }
@@ -1075,7 +1075,7 @@ void replay_attn(const ReplayAttnArgs a) {
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int rq = 0; rq < 4; ++rq)
-      *reinterpret_cast<float4 *>(pp + 4 + 32 * db + 8 * rq + 4 * half) =
+      *reinterpret_cast<float4 *>(pp + 4 + 32 * db + 8 * rq + 4 * hf) =
           make_float4(o[db][4 * rq + 0], o[db][4 * rq + 1], o[db][4 * rq + 2],
                       o[db][4 * rq + 3]);
 }
