@@ -397,9 +397,10 @@ int64_t prefill_split_limit() { return 2 * (int64_t)hwkv::device_cu_count(); }
 // launch lasts about as long as its longest block or as all tiles spread over
 // the CUs, whichever is more; splits of T tiles run in k rounds of at most
 // one per CU, each with its own start and its partial to write and merge
-// (kSplitCost tiles a round).  tiles: per head, the tiles of its first column
+// (kSplitCost tiles a round), and the merge launch and the event after it take
+// about as long as kMergeCost tiles (8 us of 1.6 us).  tiles: per head, the tiles of its first column
 // block and a bound of every block's.
-constexpr int64_t kSplitCost = 6, kSplitLeast = 4;
+constexpr int64_t kSplitCost = 6, kMergeCost = 5, kSplitLeast = 4;
 PrefillPlan plan_prefill(const std::vector<std::pair<int64_t, int64_t>> &tiles, int64_t nb) {
   PrefillPlan p;
   p.wgs = nb * (int64_t)tiles.size();
@@ -418,7 +419,7 @@ PrefillPlan plan_prefill(const std::vector<std::pair<int64_t, int64_t>> &tiles, 
     };
     int64_t T = std::max(kSplitLeast, (total + k * cus - 1) / (k * cus));
     while (T < longest && count(T) > k * cus) T += std::max<int64_t>(1, T / 16);
-    const int64_t cost = k * (T + kSplitCost);
+    const int64_t cost = k * (T + kSplitCost) + kMergeCost;
     if (T < longest && cost < best) {
       best = cost;
       p.tiles_per_split = T;
@@ -582,23 +583,7 @@ int prefill_attn_impl(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
   const int64_t p1 = pos0 + n_tokens;
   std::vector<std::pair<int64_t, int32_t>> work;  // (keys of the last token, h)
   for (int32_t h = 0; h < H; ++h) {
-    const int32_t u = layer * H + h;
-    const int64_t seq_off = (int64_t)seq * c->cap_pad[u] * D;
-    if (staged) {         // the bf16 image of the unit
-      a.head[h].k_off = SL.k_img[h];
-      a.head[h].v_off = SL.v_img[h];
-      a.head[h].pto = -1;
-      a.head[h].k_scale = c->k_scale[u];
-      a.head[h].v_scale = c->v_scale[u];
-    } else {
-      a.head[h].k_off = c->k_off[u] + seq_off;
-      a.head[h].v_off = c->v_off[u] + seq_off;
-      a.head[h].pto = page_tab_off(c, u, seq);
-      a.head[h].k_scale = 1.0f;
-      a.head[h].v_scale = 1.0f;
-    }
-    a.head[h].window = (int32_t)c->window[u];
-    const int64_t w = c->window[u];
+    const int64_t w = c->window[layer * H + h];
     work.push_back({w == 0 ? p1 : std::min(p1, (int64_t)p.n_sinks + w), h});
   }
   std::stable_sort(work.begin(), work.end(),
@@ -606,7 +591,26 @@ int prefill_attn_impl(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
                       const std::pair<int64_t, int32_t> &y) {
                      return x.first > y.first;
                    });
-  for (int32_t r = 0; r < H; ++r) a.head_order[r] = work[r].second;
+  for (int32_t r = 0; r < H; ++r) {
+    const int32_t h = work[r].second, u = layer * H + h;
+    const int64_t seq_off = (int64_t)seq * c->cap_pad[u] * D;
+    hwkv::PrefillAttnHead &hd = a.head[r];
+    if (staged) {         // the bf16 image of the unit
+      hd.k_off = SL.k_img[h];
+      hd.v_off = SL.v_img[h];
+      hd.pto = -1;
+      hd.k_scale = c->k_scale[u];
+      hd.v_scale = c->v_scale[u];
+    } else {
+      hd.k_off = c->k_off[u] + seq_off;
+      hd.v_off = c->v_off[u] + seq_off;
+      hd.pto = page_tab_off(c, u, seq);
+      hd.k_scale = 1.0f;
+      hd.v_scale = 1.0f;
+    }
+    hd.window = (int32_t)c->window[u];
+    hd.h = h;
+  }
   const int64_t cols = n_tokens * G;
   const int64_t per = hwkv::prefill_attn_columns_per_block();
   const int64_t nb = (cols + per - 1) / per;
@@ -619,7 +623,7 @@ int prefill_attn_impl(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
   std::vector<std::pair<int64_t, int64_t>> tiles(H);
   const int64_t span = (per + G - 2) / G;
   for (int32_t r = 0; r < H; ++r) {
-    const int64_t W = a.head[a.head_order[r]].window, KT = hwkv::prefill_keys((int)D);
+    const int64_t W = a.head[r].window, KT = hwkv::prefill_keys((int)D);
     const int64_t first = hwkv::prefill_tiles(
         (int)KT, (int)pos0, (int)(pos0 + (std::min(per, cols) - 1) / G), p.n_sinks, (int)W);
     const int64_t all = (p1 + KT - 1) / KT, sinks = (p.n_sinks + KT - 1) / KT;
@@ -639,11 +643,12 @@ int prefill_attn_impl(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
   a.tiles_per_split = (int32_t)plan.tiles_per_split;
   int64_t begin = 0;
   for (int32_t r = 0; r < H; ++r) {
-    a.wg_begin[r] = (int32_t)begin;
+    a.head[r].wg_begin = (int32_t)begin;
     begin += nb * ((tiles[r].second + plan.tiles_per_split - 1) / plan.tiles_per_split);
   }
-  a.wg_begin[H] = (int32_t)begin;
-  for (int32_t r = H + 1; r <= hwkv::kMaxItems; ++r) a.wg_begin[r] = INT32_MAX;
+  a.n_wgs = (int32_t)begin;
+  a.split = parts != nullptr;
+  for (int32_t r = H; r < hwkv::kMaxItems; ++r) a.head[r].wg_begin = INT32_MAX;
   if (parts) {
     a.part_acc = parts->ptr;
     a.part_ml = parts->ptr + (size_t)prefill_split_limit() * per * p.head_dim;

@@ -161,7 +161,7 @@ struct PageUpdateArgs {
 
 // Prefill attention of one chunk [p0, p0 + n_tokens) of one sequence: per
 // kv head the (unit, sequence) region offsets and canonical window; the
-// kernel's workgroups visit heads in head_order (most keys first) and each
+// kernel's workgroups visit heads in order (most keys first) and each
 // head's column blocks from the last token down.
 struct PrefillAttnHead {
   int64_t k_off;                 // element offset of the (unit, seq) K tiles
@@ -170,11 +170,12 @@ struct PrefillAttnHead {
   int32_t pto;                   // page-table offset of a paged unit, or -1
   float k_scale;                 // logit multiplier of the stored keys (fp8: s_K)
   float v_scale;                 // output multiplier (fp8: s_V)
+  int32_t h;                     // the kv head
+  int32_t wg_begin;              // first workgroup of the head
 };
 
 struct PrefillAttnArgs {
-  PrefillAttnHead head[kMaxItems];
-  int32_t head_order[kMaxItems];
+  PrefillAttnHead head[kMaxItems];   // in launch order; wg_begin INT32_MAX past the last
   const uint16_t *cache;         // 2-byte elements: bf16 or binary16
   const int32_t *page_table;     // paged caches (else null)
   int64_t pool_off;              // element offset of page 0
@@ -189,14 +190,14 @@ struct PrefillAttnArgs {
   int32_t n_sinks;
   int32_t n_col_blocks;          // per head: ceil(n_tokens * G / columns)
   float scale_log2;              // scale * log2(e)
-  // Split keys: the r-th head of head_order has workgroups [wg_begin[r],
-  // wg_begin[r + 1]), split by split, each split over the column blocks from
-  // the last token down; split j of a column block adds its key tiles
-  // [j T, (j + 1) T), T = tiles_per_split, and a block of more than T tiles
-  // leaves one partial per split for prefill_merge (workgroup w: acc rows
+  // Split keys: a head's workgroups go split by split, each split over the
+  // column blocks from the last token down; split j of a column block adds its
+  // key tiles [j T, (j + 1) T), T = tiles_per_split, and a block of more than T
+  // tiles leaves one partial per split for prefill_merge (workgroup w: acc rows
   // part_acc[w][column][D], (m, l) pairs part_ml[w][column][2], m in base-2
   // logit units).
-  int32_t wg_begin[kMaxItems + 1];   // INT32_MAX past the last head's end
+  int32_t n_wgs;                 // of all heads
+  int32_t split;                 // whether any block has more than one split
   int32_t tiles_per_split;
   float *part_acc, *part_ml;
 };

@@ -49,11 +49,21 @@
 // (tiles_per_split), whose partials prefill_merge adds up.  512 tokens at 48K
 // of context, head_dim 128: 1,717 -> 153 us with both changes (206 by this
 // one); 1,999 tokens at 30K over fp8, head_dim 256: 1,450 -> 672 (801).
+// A split is made only where it also pays for the merge launch.
+//
+// Short launches (a few tiles) are bound by the latency of the chain before
+// the first tile, its mask and the output: the arguments come in two rounds of
+// scalar loads, q and the first two tiles' loads are in flight together, a
+// partly visible tile is masked by bits (keep_rows), the rows go out through
+// LDS (store_rows), and one to two tiles run without the phase shift.  64
+// tokens of 8 heads, head_dim 128, keys 64 / 128 / 256 / 512: 13.3 / 15.0 /
+// 17.7 / 22.9 -> 10.8 / 13.0 / 15.3 / 20.0 us; a prompt of 2,901 tokens in 2
+// layers with its first decode step: 338 -> 307 us.
 //
 // Data movement.  K and V tiles go from global memory straight into LDS
 // (buffer_load_dwordx4 ... lds: lane i of an instruction fills bytes
 // [16i, 16i + 16) of the instruction's LDS block; each lane picks its own
-// source), in four stages (two in the calibration replay), no staging
+// source), in four stages, no staging
 // registers.  Both are stored as rows of one 16-byte channel chunk for the 32
 // keys of a block (512 B), two rows per load instruction; in odd rows key k sits at
 // position k ^ 4.  Lane L of every load then fetches key (L % 32) ^
@@ -182,8 +192,33 @@ __device__ __forceinline__ int lane_now() {
 // no instruction moves across this point
 __device__ __forceinline__ void pin() { __builtin_amdgcn_sched_barrier(0); }
 
+// at most LEFT vector loads of the wave are still in flight
+template <int LEFT = 0>
 __device__ __forceinline__ void wait_loads() {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"i"(LEFT) : "memory");
+}
+
+// -inf for the logits of a block whose bit is clear: row r of st holds key e +
+// cr of the lane, cr = 8 (r / 4) + r % 4, and word has bit cr for it.  Two
+// instructions a logit (a comparison for each bound takes three to eight).
+__device__ __forceinline__ void keep_rows(f32x16_t &st, uint32_t word) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const uint32_t keep =
+        (uint32_t)__builtin_amdgcn_sbfe((int)word, (r >> 2) * 8 + (r & 3), 1);
+    const float x = st[r];
+    st[r] = __builtin_bit_cast(float,
+                               (__builtin_bit_cast(uint32_t, x) & keep) | (0xff800000u & ~keep));
+  }
+}
+
+// bits [0, x), for x of any value; bit 31 stays clear
+__device__ __forceinline__ uint32_t below(int x) { return (1u << min(max(x, 0), 31)) - 1; }
+
+// LDS accesses of a wave's lanes stay in order across this point
+__device__ __forceinline__ void wave_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // x of lane l and x of lane l ^ 32 in both lanes (VALU lane swap)
@@ -304,6 +339,42 @@ __device__ __forceinline__ float tile_max(const f32x16_t (&st)[U]) {
   return max_of(lo, hi);
 }
 
+// Writes a wave's columns, O^T times inv, as rows of D floats: column c's row
+// (in the lane c and c + 32) at dst + row * stride, for columns up to last.
+// Through LDS (area: 128 CH bytes of the wave's own): a lane holds 4
+// channels in 8 of its column, and written from there an instruction would
+// touch 32 rows, 32 bytes each; a workgroup's rows took 5,000 cycles at
+// head_dim 128.  CH channels a pass, 16-byte chunks swizzled by the column.
+template <int D, int CH>
+__device__ __forceinline__ void store_rows(const f32x16_t (&o)[D / 32], float inv, float *dst,
+                                           int stride, uint32_t row, int last, uint8_t *area) {
+  constexpr int NC = CH / 4, RPI = 64 / NC;
+  const int ln = lane_now();
+  auto at = [&](int col, int chunk) {
+    return reinterpret_cast<float4 *>(area + (col * NC + (chunk ^ (col & (NC - 1)))) * 16);
+  };
+#pragma unroll
+  for (int p = 0; p < D / CH; ++p) {
+#pragma unroll
+    for (int x = 0; x < NC / 2; ++x) {             // chunk 2x + half of the pass
+      const int db = (p * CH + 8 * x) / 32, rq = (p * CH + 8 * x) / 8 % 4;
+      *at(ln & 31, 2 * x + (ln >> 5)) =
+          make_float4(o[db][4 * rq + 0] * inv, o[db][4 * rq + 1] * inv, o[db][4 * rq + 2] * inv,
+                      o[db][4 * rq + 3] * inv);
+    }
+    wave_order();
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+      const int col = i * RPI + ln / NC, chunk = ln % NC;
+      const float4 v = *at(col, chunk);
+      const uint32_t rw = (uint32_t)__shfl((int)row, col);
+      if (col <= last)
+        *reinterpret_cast<float4 *>(dst + (size_t)rw * stride + p * CH + chunk * 4) = v;
+    }
+    wave_order();
+  }
+}
+
 // Every wave's LDS reads are done, and the loads it waited for are in LDS.
 __device__ __forceinline__ void phase_end() {
   asm volatile("" ::: "memory");
@@ -317,7 +388,7 @@ template <int D, int NW, bool F16>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void prefill_attn(const PrefillAttnArgs a) {
   using P = Prefill<D, NW>;
-  constexpr int KS = P::KS, DB = P::DB, DC = P::DC;
+  constexpr int KS = P::KS, DB = P::DB;
   constexpr int KT = prefill_keys(D);               // keys per tile
   constexpr int U = KT / kKeys;                     // blocks of 32 keys per tile
   constexpr int NH = NW / U;                        // waves loading each block
@@ -326,15 +397,26 @@ void prefill_attn(const PrefillAttnArgs a) {
   static_assert(NW == 8 && P::NINST % NH == 0, "two groups of waves; tile loads");
   __shared__ __attribute__((aligned(1024))) uint8_t smem[STAGES * U * P::STAGE];
 
+  // Every argument that does not depend on the head, in one round of scalar
+  // loads; then the head's.
+  asm volatile("" ::"s"(a.cache), "s"(a.page_table), "s"(a.pool_off), "s"(a.q), "s"(a.k), "s"(a.v),
+               "s"(a.p0), "s"(a.n_tokens), "s"(a.n_kv_heads), "s"(a.group), "s"(a.n_sinks),
+               "s"(a.n_col_blocks), "s"(a.scale_log2), "s"(a.split), "s"(a.tiles_per_split));
   const int nb = a.n_col_blocks;
   const int blk = blockIdx.x;
-  // the head: the number of heads that begin at or before this workgroup
-  const int rank = __builtin_amdgcn_readfirstlane(
-      __popcll(__ballot(a.wg_begin[threadIdx.x & 63] <= blk)) - 1);
-  const int split = (blk - a.wg_begin[rank]) / nb;
-  const int h = a.head_order[rank];
-  const int cb = nb - 1 - (blk - a.wg_begin[rank]) % nb;   // later tokens first
-  const PrefillAttnHead &hd = a.head[h];
+  // The head: heads have nb workgroups each, or where keys are split the head
+  // is the number of those that begin at or before this workgroup.
+  int rank = blk / nb;
+  if (a.split)
+    rank = __builtin_amdgcn_readfirstlane(
+        __popcll(__ballot(a.head[threadIdx.x & 63].wg_begin <= blk)) - 1);
+  const PrefillAttnHead &hd = a.head[rank];
+  asm volatile("" ::"s"(hd.k_off), "s"(hd.v_off), "s"(hd.window), "s"(hd.pto), "s"(hd.k_scale),
+               "s"(hd.v_scale), "s"(hd.h), "s"(hd.wg_begin));
+  const int h = hd.h, pto = hd.pto;
+  const int run0 = blk - hd.wg_begin;
+  const int split = run0 / nb;
+  const int cb = nb - 1 - (run0 - split * nb);      // later tokens first
   const int G = a.group;
   const int Hq = a.n_kv_heads * G;
   const int ncols = a.n_tokens * G;
@@ -360,9 +442,7 @@ void prefill_attn(const PrefillAttnArgs a) {
   const bool wave_live = wc0 <= c_last;
   const int wc_last = min(wc0 + 31, c_last);
   const int t_lo = pos(min(wc0, c_last) / G), t_hi = pos(wc_last / G);
-  const int c = wc0 + cl;
-  const bool col_ok = c <= c_last;
-  const int cc = min(c, c_last);
+  const int cc = min(wc0 + cl, c_last);
   const int tl = cc / G, g = cc - tl * G;
   const size_t q_row = ((size_t)tl * Hq + (size_t)h * G + g) * D;
 
@@ -386,7 +466,7 @@ void prefill_attn(const PrefillAttnArgs a) {
   u32x4_t qv[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
-    qv[ks] = col_ok ? ld16(a.q + q_row + 16 * ks + 8 * half) : u32x4_t{0, 0, 0, 0};
+    qv[ks] = ld16(a.q + q_row + 16 * ks + 8 * half);   // past the last column: its copy
 
   const uint16_t *kc = a.cache + hd.k_off;
   const uint16_t *vc = a.cache + hd.v_off;
@@ -431,7 +511,7 @@ void prefill_attn(const PrefillAttnArgs a) {
   // change under the kernel)
   auto page_of = [&](int s0) -> const uint8_t * {
     const int pg = ((const __attribute__((address_space(4))) int32_t *)
-                        a.page_table)[__builtin_amdgcn_readfirstlane(hd.pto + (s0 >> 8))];
+                        a.page_table)[__builtin_amdgcn_readfirstlane(pto + (s0 >> 8))];
     return reinterpret_cast<const uint8_t *>(a.cache + a.pool_off + (int64_t)pg * 2 * kPageTokens * D);
   };
   auto issue_loads = [&](int it, uint8_t *stage) {
@@ -447,7 +527,7 @@ void prefill_attn(const PrefillAttnArgs a) {
         len = se - s0;
       } else if (W == 0) {
         len = ce - s0;
-        if (hd.pto >= 0) {
+        if (pto >= 0) {
           kb = page_of(s0);
           vb = kb + kPageTokens * D * 2;
           sl0 = s0 & (kPageTokens - 1);
@@ -498,7 +578,7 @@ void prefill_attn(const PrefillAttnArgs a) {
         }
         int sl = s;
         if (W != 0 && s >= S) sl = S + (s - S) % W;
-        if (hd.pto >= 0) {
+        if (pto >= 0) {
           sl &= kPageTokens - 1;
           if (s0 >= ce) kb = kcb;                   // no cached key: nothing is read
         }
@@ -526,6 +606,8 @@ void prefill_attn(const PrefillAttnArgs a) {
   // vector register to spare for it)
   float c2 = __builtin_bit_cast(
       float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.scale_log2 * hd.k_scale)));
+  float v_scale = hd.v_scale;
+  asm volatile("" : "+s"(v_scale));              // loaded here, not after the loop
   if constexpr (F16) {
     // q to binary16 under the wavefront's power of two 2^sh; c2 takes 2^-sh
     // (sh is capped so that c2 stays a normal number)
@@ -582,25 +664,15 @@ void prefill_attn(const PrefillAttnArgs a) {
   // has none to spare)
   asm volatile("" : "+v"(klane), "+v"(vlane));
 
-  // masks the block of keys from s0 on, unless every column sees all of it
-  auto mask = [&](f32x16_t &st, int s0, int se) {
-    const int slast = min(s0 + kKeys, se) - 1;
-    const bool full_vis = s0 + kKeys <= se && slast <= t_lo &&
-                          (W == 0 || slast < S || s0 >= t_hi + 1 - W);
-    if (!full_vis) {
-      // key of row r: e + cr, cr = 8 (r / 4) + r % 4; e and e - t are made
-      // opaque so the per-row offsets stay compile-time constants on the
-      // uniform side of each comparison
-      const int cx = wc0 + (lane_now() & 31);
-      int e = s0 + 4 * (lane_now() >> 5), d = e - pos(min(cx, c_last) / G);
-      asm volatile("" : "+v"(e), "+v"(d));
+  // masks the tile of keys [s0, min(s0 + KT, se))
+  auto mask = [&](f32x16_t (&st)[U], int s0, int se) {
+    const int tm = pos(min(wc0 + (lane_now() & 31), c_last) / G);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int cr = (r >> 2) * 8 + (r & 3);
-        const bool vis = (e < se - cr) & (d <= -cr) &
-                         ((W == 0) | (e < S - cr) | (d >= 1 - W - cr));
-        if (!vis) st[r] = -__builtin_inff();
-      }
+    for (int u = 0; u < U; ++u) {
+      const int e = s0 + kKeys * u + 4 * (lane_now() >> 5);
+      uint32_t vis = below(min(se, tm + 1) - e);
+      if (W != 0) vis &= below(S - e) | ~below(tm + 1 - W - e);
+      keep_rows(st[u], vis);
     }
   };
   // raises the shift (and rescales the sums) where a tile's maximum exceeds it
@@ -639,16 +711,20 @@ void prefill_attn(const PrefillAttnArgs a) {
     const int slast = min(s0 + KT, se) - 1;
     return wave_live && s0 <= t_hi && !(W != 0 && s0 >= S && slast < t_lo + 1 - W);
   };
+  constexpr int SB = U * P::STAGE;               // bytes of a stage
+#pragma unroll 1
+  for (int it = 0; it < min(n_it, 2); ++it) issue_loads(it, smem + it * SB);
+  if (n_it > 1)
+    wait_loads<2 * IPW>();
+  else
+    wait_loads();
   // q has arrived before the loop: a wait for it inside would wait for the
   // tiles' loads too
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qv[ks]));
-  constexpr int SB = U * P::STAGE;               // bytes of a stage
-  issue_loads(0, smem);
-  if (n_it > 1) issue_loads(1, smem + SB);
-  wait_loads();
   phase_end();
-  const bool late = wave >= NW / 2;              // the second group
+  // the second group (together with the first where there is little to overlap)
+  const bool late = wave >= NW / 2 && n_it > 2;
   if (late) phase_end();
 
   f32x16_t st[U];                                // S^T of the tile
@@ -675,8 +751,7 @@ void prefill_attn(const PrefillAttnArgs a) {
       if (!whole) {
         int s0, se;
         tile_range(i_lo + it, &s0, &se);
-#pragma unroll
-        for (int u = 0; u < U; ++u) mask(st[u], s0 + kKeys * u, se);
+        mask(st, s0, se);
       }
       raise(tile_max(st));
       tile_weights<U, F16>(st, pb, l, c2, m * c2 - pbias);
@@ -689,36 +764,31 @@ void prefill_attn(const PrefillAttnArgs a) {
 
   float l_lo, l_hi;
   halves(l, &l_lo, &l_hi);
-  // the lane's column and output row, recomputed rather than kept live
-  // through the loop
-  const int c_out = wc0 + (lane_now() & 31);
-  const int half_o = lane_now() >> 5;
-  if (c_out > c_last) return;
   const float lt = l_lo + l_hi;
-  float inv;
-  float *orow;
+  // The lane's column and its output row, recomputed rather than kept live
+  // through the loop.
+  const int c_out = wc0 + (lane_now() & 31);
+  float inv = 1.0f;
+  float *dst = a.out;
+  uint32_t row;                                    // of D floats
   if (n_it == ntiles) {
-    inv = hd.v_scale / lt;               // the stored values' scale (fp8)
-    const int tl_o = c_out / G, g_o = c_out - tl_o * G;
-    orow = a.out + ((size_t)tl_o * Hq + (size_t)h * G + g_o) * D;
+    inv = v_scale / lt;                            // the stored values' scale (fp8)
+    const int tl_o = min(c_out, c_last) / G;
+    row = (uint32_t)tl_o * (Hq - G) + h * G + c_out;
   } else {
-    inv = 1.0f;
-    const size_t pc = (size_t)blk * (32 * NW) + (c_out - c_first);
-    orow = a.part_acc + pc * D;
-    if (half_o == 0)
-      *reinterpret_cast<float2 *>(a.part_ml + pc * 2) = make_float2(fmaxf(m * c2, -3e38f), lt);
+    dst = a.part_acc;
+    row = (uint32_t)blk * (32 * NW) + (c_out - c_first);
+    if (c_out <= c_last && lane_now() < 32)
+      *reinterpret_cast<float2 *>(a.part_ml + (size_t)row * 2) =
+          make_float2(fmaxf(m * c2, -3e38f), lt);
   }
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int rq = 0; rq < 4; ++rq) {
-      float4 v;
-      v.x = o[db][4 * rq + 0] * inv;
-      v.y = o[db][4 * rq + 1] * inv;
-      v.z = o[db][4 * rq + 2] * inv;
-      v.w = o[db][4 * rq + 3] * inv;
-      *reinterpret_cast<float4 *>(orow + 32 * db + 8 * rq + 4 * half_o) = v;
-    }
+  constexpr int CH = D > 64 ? 64 : 32, AREA = 128 * CH;
+  static_assert(NW / 2 * AREA <= SB && STAGES >= 4, "two stages hold every wave's area");
+  // two stages that the other group's last products do not read
+  const int stage = so + (wave < NW / 2 ? SB : 2 * SB);
+  store_rows<D, CH>(o, inv, dst, D, row, c_last - wc0,
+                smem + (stage >= STAGES * SB ? stage - STAGES * SB : stage) +
+                    wave % (NW / 2) * AREA);
 }
 
 // Merge of the split partials: one row of D / 4 lanes per column, a lane
@@ -740,9 +810,11 @@ __global__ __launch_bounds__(256) void prefill_merge(const PrefillAttnArgs a) {
   const int G = a.group, Hq = a.n_kv_heads * G;
   const int c_first = cb * COLS;
   const int c_last = min(c_first + COLS, a.n_tokens * G) - 1;
-  const int h = a.head_order[rank];
+  const PrefillAttnHead &hd = a.head[rank];
+  const int h = hd.h;
   const int T = a.tiles_per_split;
-  const int nt = prefill_tiles(prefill_keys(D), a.p0 + c_first / G, a.p0 + c_last / G, a.n_sinks, a.head[h].window);
+  const int nt = prefill_tiles(prefill_keys(D), a.p0 + c_first / G, a.p0 + c_last / G, a.n_sinks,
+                               hd.window);
   if (nt <= T) return;                             // uniform: written by its one split
   const int ns = (nt + T - 1) / T;
   const int col = x % PER * CPW + threadIdx.x / LPC;   // column of the block
@@ -750,7 +822,7 @@ __global__ __launch_bounds__(256) void prefill_merge(const PrefillAttnArgs a) {
   if (c > c_last) return;
   const int ch = threadIdx.x % LPC * 4;
   // split j's workgroup is w0 + j nb
-  const size_t w0 = (size_t)a.wg_begin[rank] + (nb - 1 - cb);
+  const size_t w0 = (size_t)hd.wg_begin + (nb - 1 - cb);
   const float *acc = a.part_acc + (w0 * COLS + col) * D + ch;
   const float *ml = a.part_ml + (w0 * COLS + col) * 2;
   const size_t step = (size_t)nb * COLS;
@@ -789,7 +861,7 @@ __global__ __launch_bounds__(256) void prefill_merge(const PrefillAttnArgs a) {
     }
     M = Mn;
   }
-  const float inv = a.head[h].v_scale / L;
+  const float inv = hd.v_scale / L;
   const int tl = c / G, g = c - tl * G;
   *reinterpret_cast<float4 *>(a.out + ((size_t)tl * Hq + (size_t)h * G + g) * D + ch) =
       make_float4(A.x * inv, A.y * inv, A.z * inv, A.w * inv);
@@ -873,9 +945,8 @@ void replay_attn(const ReplayAttnArgs a) {
   u32x4_t qv[KS];
   {
     const uint16_t *qr = a.q + column_id() * D + 8 * half;
-    const bool ok = wc0 + cl <= c_last;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qv[ks] = ok ? ld16(qr + 16 * ks) : u32x4_t{0, 0, 0, 0};
+    for (int ks = 0; ks < KS; ++ks) qv[ks] = ld16(qr + 16 * ks);
   }
 
   // Tile loads: chunk rows 2n, 2n + 1 by wave n % NW (see prefill_attn), from
@@ -917,15 +988,17 @@ void replay_attn(const ReplayAttnArgs a) {
   int vlane = P::KBYTES + (gq & 1) * P::VPAIR + vpar * 512 + (vkey0 ^ (4 * vpar)) * 16 +
               (mq & 1) * 8;
   asm volatile("" : "+v"(klane), "+v"(vlane), "+v"(vo));
+#pragma unroll 1
+  for (int it = 0; it < min(n_it, 2); ++it) {
+    const bool past = it == 0 && (i_hi - 1) * kKeys + (cl ^ (4 * half)) > tb;
+    issue_loads(smem + it * P::STAGE, past ? kNoRow : vo);
+  }
+  if (P::NINST % NW == 0 && n_it > 1)
+    wait_loads<2 * P::IPW>();                    // the first tile has landed
+  else
+    wait_loads();
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qv[ks]));
-
-  {
-    const int s = (i_hi - 1) * kKeys + (cl ^ (4 * half));
-    issue_loads(smem, s <= tb ? vo : kNoRow);
-  }
-  if (n_it > 1) issue_loads(smem + P::STAGE, vo);
-  wait_loads();
   __syncthreads();                               // swin too
   // The lane's next window: the first whose edge lies below this split's top
   // (windows with an edge at or above it have no key here).  An edge at or
@@ -941,7 +1014,8 @@ void replay_attn(const ReplayAttnArgs a) {
     edge = edge_of(kn);
   }
   phase_end();
-  const bool late = wave >= NW / 2;              // the second group
+  // the second group (together with the first where there is little to overlap)
+  const bool late = wave >= NW / 2 && n_it > 2;
   if (late) phase_end();
 
   f32x16_t st[1];                                // S^T of the tile
@@ -1085,7 +1159,7 @@ void replay_attn(const ReplayAttnArgs a) {
 int prefill_attn_columns_per_block() { return 32 * kPrefillWaves; }
 
 hipError_t launch_prefill_attn(int D, bool f16, const PrefillAttnArgs &a, hipStream_t s) {
-  const dim3 grid((unsigned)a.wg_begin[a.n_kv_heads]);
+  const dim3 grid((unsigned)a.n_wgs);
   const dim3 block(kPrefillWaves * 64);
 #define HWKV_PA(DD, FF) \
   hipLaunchKernelGGL((prefill_attn<DD, kPrefillWaves, FF>), grid, block, 0, s, a)
