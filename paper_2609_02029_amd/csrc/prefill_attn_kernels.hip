@@ -880,6 +880,14 @@ __global__ __launch_bounds__(256) void prefill_merge(const PrefillAttnArgs a) {
 // the rest.  Split y < n_splits covers key tiles [y tps, (y + 1) tps) of
 // [0, t_last] without the sinks; split n_splits adds the sinks alone.
 // replay_merge assembles each candidate.
+//
+// Where the sampled rows lie far apart nearly every tile of the top splits
+// holds an edge of some row, and these passes, which the barriers make every
+// wave wait for, are most of the time: a row's edges in tiles of their own
+// take a pass each.  Their masks by bits (keep_rows) rather than by two
+// comparisons a logit, and the last rows written through LDS, took a 20,011-key
+// fp8 trace's replay (101 rows, head_dim 128) from 291 to 269 us; 256 rows of a
+// 128K trace at head_dim 256, where few tiles hold an edge, stay at 819.
 template <int D, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void replay_attn(const ReplayAttnArgs a) {
@@ -1079,14 +1087,9 @@ void replay_attn(const ReplayAttnArgs a) {
       }
       // visible keys: s <= t, and s < S in the sink pass, s >= S otherwise
       if (!(s0 + kKeys - 1 <= t_lo && (sink_pass ? s0 + kKeys <= S : s0 >= S))) {
-        int e = s0 + 4 * (lane_now() >> 5), d = e - t;
-        asm volatile("" : "+v"(e), "+v"(d));
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int cr = (r >> 2) * 8 + (r & 3);
-          const bool seen = (d <= -cr) & (sink_pass ? (e < S - cr) : (e >= S - cr));
-          if (!seen) st[0][r] = -__builtin_inff();
-        }
+        const int e = s0 + 4 * (lane_now() >> 5);
+        const uint32_t sinks = below(S - e);
+        keep_rows(st[0], below(t + 1 - e) & (sink_pass ? sinks : ~sinks));
       }
       if (first) {
         const float mx = tile_max(st);
@@ -1111,19 +1114,17 @@ void replay_attn(const ReplayAttnArgs a) {
       lo = act ? edge : s0;
       const float mc = m * c2;
       const int e = s0 + 4 * (lane_now() >> 5);
+      keep_rows(st[0], below(cut - e) & ~below(lo - e));
       float ls = 0.0f;
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int r0 = 8 * s + 2 * j, r1 = r0 + 1;
-          const int k0 = e + (r0 >> 2) * 8 + (r0 & 3), k1 = e + (r1 >> 2) * 8 + (r1 & 3);
           const float w0 = __builtin_amdgcn_exp2f(__builtin_fmaf(st[0][r0], c2, -mc));
           const float w1 = __builtin_amdgcn_exp2f(__builtin_fmaf(st[0][r1], c2, -mc));
-          const float p0 = (k0 >= lo && k0 < cut) ? w0 : 0.0f;
-          const float p1 = (k1 >= lo && k1 < cut) ? w1 : 0.0f;
-          ls += p0 + p1;
-          pb[s][j] = pack_bf16(p0, p1);
+          ls += w0 + w1;
+          pb[s][j] = pack_bf16(w0, w1);
         }
       l += ls;
       if (!edges) break;
@@ -1138,20 +1139,18 @@ void replay_attn(const ReplayAttnArgs a) {
 
   float l_lo, l_hi;
   halves(l, &l_lo, &l_hi);
-  if (wc0 + (lane_now() & 31) > c_last) return;
-  const int hf = lane_now() >> 5;
-  float *pp = a.part + ((size_t)blockIdx.y * n_cols + column_id()) * (D + 4);
-  if (hf == 0) {
+  const uint32_t row = (uint32_t)(blockIdx.y * n_cols + column_id());
+  float *pp = a.part + (size_t)row * (D + 4);
+  if (lane_now() < 32 && wc0 + lane_now() <= c_last) {
     pp[0] = m;
     pp[1] = l_lo + l_hi;
   }
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int rq = 0; rq < 4; ++rq)
-      *reinterpret_cast<float4 *>(pp + 4 + 32 * db + 8 * rq + 4 * hf) =
-          make_float4(o[db][4 * rq + 0], o[db][4 * rq + 1], o[db][4 * rq + 2],
-                      o[db][4 * rq + 3]);
+  constexpr int SB = P::STAGE, CH = D / 4, AREA = 128 * CH;
+  static_assert(NW / 2 * AREA <= SB && STAGES >= 4, "two stages hold every wave's area");
+  const int stage = so + (wave < NW / 2 ? SB : 2 * SB);   // as in prefill_attn
+  store_rows<D, CH>(o, 1.0f, a.part + 4, D + 4, row, c_last - wc0,
+                smem + (stage >= STAGES * SB ? stage - STAGES * SB : stage) +
+                    wave % (NW / 2) * AREA);
 }
 
 }  // namespace
