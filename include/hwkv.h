@@ -265,7 +265,11 @@ int hwkv_prefill_write(hwkv_cache *cache, int32_t layer, int32_t seq,
  * ECAPACITY if pos0 + n_tokens > max_ctx; EINVAL on bad indices, null
  * pointers, a non-finite or non-positive scale, or a cache whose format is
  * not bf16 (hwkv_prefill_attn_ws takes every format); n_tokens == 0 is a
- * no-op. */
+ * no-op.
+ * A launch that would leave CUs idle splits its keys; the partials go into
+ * device buffers that the library keeps, at most two per device, while a cache
+ * that used them lives.  Calls of any stream or thread may share them; without
+ * one at hand, or while `stream` is captured, the keys are not split. */
 int hwkv_prefill_attn(hwkv_cache *cache, int32_t layer, int32_t seq,
                       int64_t pos0, int64_t n_tokens, const void *q,
                       const void *k, const void *v, float scale, void *out,

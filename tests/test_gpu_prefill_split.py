@@ -39,6 +39,23 @@ def test_few_tokens_over_many_keys(fmt, paged, D, G, S, windows, cuts):
     r.free()
 
 
+# launches of one to three key tiles (without and with the phase shift), whose
+# tiles are all partly visible: chunks that end at, before and past the edges
+# of a mask's word, a tile and a block of columns
+@pytest.mark.parametrize("D,G,S,windows", [
+    (64, 1, 0, [1, 33, 0]), (128, 3, 31, [32, 64, 0]), (256, 6, 1, [30, 65, 0]),
+])
+def test_few_keys(D, G, S, windows):
+    cuts = [1, 2, 32, 63, 65, 97, 128, 160]
+    cfg = mini(head_dim=D, n_q_heads=3 * G, n_kv_heads=3, n_sinks=S, level_windows=windows,
+               levels=[[0, 1, 2]], prompt=[193], max_ctx=200, seed=53)
+    r = Run(cfg)
+    q, qh, out = r.prefill_with_attn(0, 0, chunks=cuts)
+    check_rows(r, 0, 0, np.arange(193), qh, out, f"D={D} {windows}")
+    r.check_layer(0)
+    r.free()
+
+
 def _pair(seed):
     """Two sequences of 4,000 cached tokens, and a 40-token chunk of each."""
     cfg = mini(batch=2, head_dim=128, n_q_heads=8, level_windows=[700, 0], prompt=[4000, 4000],
