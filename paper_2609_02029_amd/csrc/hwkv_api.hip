@@ -716,6 +716,7 @@ int prefill_attn_impl(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
   a.n_tokens = (int32_t)n_tokens;
   a.n_kv_heads = H;
   a.group = G;
+  a.group_inv = (uint32_t)((1 << 24) / G + 1);
   a.n_sinks = p.n_sinks;
   a.n_col_blocks = (int32_t)nb;
   a.scale_log2 = scale * 1.4426950408889634f;

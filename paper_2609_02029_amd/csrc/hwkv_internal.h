@@ -199,6 +199,7 @@ struct PrefillAttnArgs {
   int32_t n_wgs;                 // of all heads
   int32_t split;                 // whether any block has more than one split
   int32_t tiles_per_split;
+  uint32_t group_inv;            // 2^24 / G + 1
   float *part_acc, *part_ml;
 };
 

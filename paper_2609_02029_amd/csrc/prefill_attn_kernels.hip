@@ -212,6 +212,14 @@ __device__ __forceinline__ void keep_rows(f32x16_t &st, uint32_t word) {
   }
 }
 
+// x / G, inv = 2^24 / G + 1, for x < G + 255 (a block's columns, from its first
+// token's first): exact, since x * inv < 2^32 and its error, at most x G, stays
+// below 2^24.  A division takes some hundred cycles, and a launch of one tile
+// waits for six of them.
+__device__ __forceinline__ int token_of(int x, uint32_t inv) {
+  return (int)(((uint32_t)x * inv) >> 24);
+}
+
 // bits [0, x), for x of any value; bit 31 stays clear
 __device__ __forceinline__ uint32_t below(int x) { return (1u << min(max(x, 0), 31)) - 1; }
 
@@ -401,21 +409,23 @@ void prefill_attn(const PrefillAttnArgs a) {
   // loads; then the head's.
   asm volatile("" ::"s"(a.cache), "s"(a.page_table), "s"(a.pool_off), "s"(a.q), "s"(a.k), "s"(a.v),
                "s"(a.p0), "s"(a.n_tokens), "s"(a.n_kv_heads), "s"(a.group), "s"(a.n_sinks),
-               "s"(a.n_col_blocks), "s"(a.scale_log2), "s"(a.split), "s"(a.tiles_per_split));
+               "s"(a.n_col_blocks), "s"(a.scale_log2), "s"(a.split), "s"(a.tiles_per_split), "s"(a.group_inv));
   const int nb = a.n_col_blocks;
   const int blk = blockIdx.x;
   // The head: heads have nb workgroups each, or where keys are split the head
   // is the number of those that begin at or before this workgroup.
-  int rank = blk / nb;
+  int rank;
   if (a.split)
     rank = __builtin_amdgcn_readfirstlane(
         __popcll(__ballot(a.head[threadIdx.x & 63].wg_begin <= blk)) - 1);
+  else
+    rank = blk / nb;
   const PrefillAttnHead &hd = a.head[rank];
   asm volatile("" ::"s"(hd.k_off), "s"(hd.v_off), "s"(hd.window), "s"(hd.pto), "s"(hd.k_scale),
                "s"(hd.v_scale), "s"(hd.h), "s"(hd.wg_begin));
   const int h = hd.h, pto = hd.pto;
   const int run0 = blk - hd.wg_begin;
-  const int split = run0 / nb;
+  const int split = a.split ? run0 / nb : 0;
   const int cb = nb - 1 - (run0 - split * nb);      // later tokens first
   const int G = a.group;
   const int Hq = a.n_kv_heads * G;
@@ -428,7 +438,11 @@ void prefill_attn(const PrefillAttnArgs a) {
   auto pos = [&](int r) -> int { return p0 + r; };
   const int S = a.n_sinks;
   const int W = hd.window;                          // 0 = full
-  const int ta = pos(c_first / G), tb = pos(c_last / G);
+  // A column's token: one division for the block's first column, the others
+  // from there by the reciprocal (exact: token_of).
+  const int t0 = c_first / G, r0 = c_first - t0 * G;
+  auto token = [&](int c) -> int { return t0 + token_of(r0 + c - c_first, a.group_inv); };
+  const int ta = pos(t0), tb = pos(token(c_last));
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -441,9 +455,9 @@ void prefill_attn(const PrefillAttnArgs a) {
   const int wc0 = c_first + 32 * wave;
   const bool wave_live = wc0 <= c_last;
   const int wc_last = min(wc0 + 31, c_last);
-  const int t_lo = pos(min(wc0, c_last) / G), t_hi = pos(wc_last / G);
+  const int t_lo = pos(token(min(wc0, c_last))), t_hi = pos(token(wc_last));
   const int cc = min(wc0 + cl, c_last);
-  const int tl = cc / G, g = cc - tl * G;
+  const int tl = token(cc), g = cc - tl * G;
   const size_t q_row = ((size_t)tl * Hq + (size_t)h * G + g) * D;
 
   // key ranges: [0, ra1) then [rb0, rb1)
@@ -666,7 +680,7 @@ void prefill_attn(const PrefillAttnArgs a) {
 
   // masks the tile of keys [s0, min(s0 + KT, se))
   auto mask = [&](f32x16_t (&st)[U], int s0, int se) {
-    const int tm = pos(min(wc0 + (lane_now() & 31), c_last) / G);
+    const int tm = pos(token(min(wc0 + (lane_now() & 31), c_last)));
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int e = s0 + kKeys * u + 4 * (lane_now() >> 5);
@@ -773,7 +787,7 @@ void prefill_attn(const PrefillAttnArgs a) {
   uint32_t row;                                    // of D floats
   if (n_it == ntiles) {
     inv = v_scale / lt;                            // the stored values' scale (fp8)
-    const int tl_o = min(c_out, c_last) / G;
+    const int tl_o = token(min(c_out, c_last));
     row = (uint32_t)tl_o * (Hq - G) + h * G + c_out;
   } else {
     dst = a.part_acc;
