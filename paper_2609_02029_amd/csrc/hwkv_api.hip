@@ -790,7 +790,8 @@ int64_t item_tiles(int64_t total, int64_t cus) {
 //     4.5 us where items are split.
 // Split where items are few and long (8 items of 2,048 slots, 128 x 4: 11.7 us
 // against 26.8), by item where there are many (512 of 2,048 slots: 95 against
-// 166; 256 of 512: 20 against 55; 2 of 128, 64 x 4: 8.7 against 10.0).
+// 166; 256 of 512: 20 against 55).  The estimates err by up to a tenth each way
+// on ragged batches, so the split stays unless the gain is clear.
 bool decode_by_item(const hwkv_cache *c, const std::vector<int64_t> &tiles) {
   const double dg = (double)c->pol.head_dim * (double)group_size(c->pol);
   const int64_t cus = hwkv::device_cu_count();
@@ -808,7 +809,7 @@ bool decode_by_item(const hwkv_cache *c, const std::vector<int64_t> &tiles) {
   const double work = 15.5e-6 * dg * slots *
                       std::max((double)std::min(longest, T), (double)total / (double)cus);
   const double item = std::max(base * rounds + work, base + bytes / 5.2e6) + (longest > T ? 4.5 : 0.0);
-  return item < 0.95 * split;
+  return item < 0.85 * split;
 }
 
 // The launches of decode_by_item: up to kItemSeqs sequences each, heads by
