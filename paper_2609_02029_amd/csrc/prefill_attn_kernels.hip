@@ -145,9 +145,11 @@ __device__ __forceinline__ f32x16_t mfma16(u32x4_t a, u32x4_t b, f32x16_t c) {
 }
 
 // 16 bytes from global memory into the LDS block of the issuing instruction, at
-// a scalar base and 32-bit byte offsets (lane's and uniform).  The descriptor spans 2^31 bytes (a unit's K or V is smaller); an access is out
-// of range, and reads as zero, where the lane's offset is at or past the span
-// less the uniform offset, so a lane offset of the span itself always is.
+// a scalar base and 32-bit byte offsets (lane's and uniform), which count from
+// the first row that an instruction reads.  The descriptor spans 2^31 bytes; an
+// access is out of range, and reads as zero, where the lane's offset is at or
+// past the span less the uniform offset, so a lane offset of the span itself
+// always is.
 constexpr uint32_t kSpan = 0x80000000u;
 constexpr int kNoRow = (int)kSpan;
 typedef u32x4_t rsrc_t;
@@ -590,16 +592,15 @@ void prefill_attn(const PrefillAttnArgs a) {
             put(reinterpret_cast<const uint8_t *>(kin + at),
                 reinterpret_cast<const uint8_t *>(vin + at), off, off, 32, stage);
         }
-        int sl = s;
-        if (W != 0 && s >= S) sl = S + (s - S) % W;
-        if (pto >= 0) {
-          sl &= kPageTokens - 1;
-          if (s0 >= ce) kb = kcb;                   // no cached key: nothing is read
-        }
+        if (pto >= 0 && s0 >= ce) kb = kcb;         // no cached key: nothing is read
         const bool cached = s < ce;
-        if (!own)
-          put(kb, vb, cached ? (sl >> 6) * TB + (sl & 63) * 16 + half * 1024 : kNoRow,
-              cached ? sl * (D * 2) + half * 16 : kNoRow, 2048, stage);
+        const int sl = pto >= 0 ? sl0 + lkey : cached_slot(s, S, W);
+        const CachedRow cr = cached_row(D, sl, sl0, S);
+        const int ck = cached ? cr.k + half * 1024 : kNoRow, cv = cached ? cr.v + half * 16 : kNoRow;
+        if (!own && cr.base == sl0)
+          put(kb + cached_base_k(D, sl0), vb + cached_base_v(D, sl0), ck, cv, 2048, stage);
+        if (!own && cr.base != sl0)                 // past the ring's wrap
+          put(kb + cached_base_k(D, S), vb + cached_base_v(D, S), ck, cv, 2048, stage);
         return;
       }
     }
