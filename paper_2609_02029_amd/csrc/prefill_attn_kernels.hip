@@ -267,8 +267,8 @@ __device__ __forceinline__ u32x4_t read_values(const uint8_t *vl, int s, int db)
 }
 
 // The products of a phase: S^T of a tile of U blocks of 32 keys (K at kl) and,
-// if VALUES, O^T += V^T P^T of the one before it (V at vl; 16 keys a step, two
-// steps a block).  They alternate, and so do the blocks of S^T: a product that
+// if VALUES, O^T += V^T P^T of the one before it (its blocks' V at vl and vl1; 16
+// keys a step, two steps a block).  They alternate, and so do the blocks of S^T: a product that
 // adds to the one before it would wait out that one's latency.  The order of
 // operand reads and products is pinned, reads kPipe products of their kind
 // ahead: left to itself the scheduler reads each operand just before its
@@ -276,7 +276,8 @@ __device__ __forceinline__ u32x4_t read_values(const uint8_t *vl, int s, int db)
 template <int D, int NW, bool F16, int U, bool VALUES>
 __device__ __forceinline__ void tile_products(f32x16_t (&o)[D / 32], f32x16_t (&st)[U],
                                               const u32x4_t (&pb)[2 * U], const u32x4_t (&qv)[D / 16],
-                                              const uint8_t *kl, const uint8_t *vl) {
+                                              const uint8_t *kl, const uint8_t *vl,
+                                              const uint8_t *vl1) {
   using P = Prefill<D, NW>;
   constexpr int KS = P::KS, DB = P::DB;
   constexpr int N = U * KS;                      // products of each kind
@@ -288,7 +289,7 @@ __device__ __forceinline__ void tile_products(f32x16_t (&o)[D / 32], f32x16_t (&
   };
   auto read_v = [&](int i) {
     const int s = i / DB, db = i % DB;
-    va[i % A] = read_values<P>(vl + (s / 2) * P::STAGE, s % 2, db);
+    va[i % A] = read_values<P>(s / 2 == 0 ? vl : vl1, s % 2, db);
   };
 #pragma unroll
   for (int i = 0; i < A; ++i) {
@@ -705,8 +706,8 @@ void prefill_attn(const PrefillAttnArgs a) {
     }
   };
   auto products = [&](auto values, f32x16_t (&st)[U], const u32x4_t (&pb)[2 * U], const uint8_t *kl,
-                      const uint8_t *vl) {
-    tile_products<D, NW, F16, U, decltype(values)::value>(o, st, pb, qv, kl, vl);
+                      const uint8_t *vl, const uint8_t *vl1) {
+    tile_products<D, NW, F16, U, decltype(values)::value>(o, st, pb, qv, kl, vl, vl1);
   };
   // Tiles [f0, f0 + fn) of this split are seen whole by every column of the
   // wave.
@@ -719,12 +720,14 @@ void prefill_attn(const PrefillAttnArgs a) {
     f1 = wave_live ? f1 - i_lo : f0;
   }
   const uint32_t fn = (uint32_t)max(f1 - f0, 0);
-  // whether any column of this wave sees a key of tile it
-  auto visible = [&](int it) {
+  // whether any column of this wave sees a key of [s0, min(s0 + n, se))
+  auto sees = [&](int s0, int n, int se) {
+    return wave_live && s0 <= t_hi && !(W != 0 && s0 >= S && min(s0 + n, se) - 1 < t_lo + 1 - W);
+  };
+  auto visible = [&](int it) {                   // of tile it
     int s0, se;
     tile_range(i_lo + it, &s0, &se);
-    const int slast = min(s0 + KT, se) - 1;
-    return wave_live && s0 <= t_hi && !(W != 0 && s0 >= S && slast < t_lo + 1 - W);
+    return sees(s0, KT, se);
   };
   constexpr int SB = U * P::STAGE;               // bytes of a stage
 #pragma unroll 1
@@ -745,33 +748,39 @@ void prefill_attn(const PrefillAttnArgs a) {
   f32x16_t st[U];                                // S^T of the tile
   u32x4_t pb[2 * U];                             // the weights of the tile, packed
   bool held = false;                             // pb holds weights to add
-  int so = 0, so1 = 0;                           // LDS offsets of tiles it, it - 1
+  int so = 0;                                    // LDS offset of tile it
+  int sv[2] = {0, 0};                            // and of the blocks whose values pb weighs
   for (int it = 0;; ++it) {
     // ---- products: S^T of tile it, then V^T P^T of tile it - 1
     const bool whole = (uint32_t)(it - f0) < fn;
     const bool vis = it < n_it && (whole || visible(it));
     __builtin_amdgcn_s_waitcnt(0xc07f);          // no scalar load outstanding: LDS waits can count
-    const uint8_t *kl = smem + so + klane, *vl = smem + so1 + vlane;
+    const uint8_t *kl = smem + so + klane, *vl = smem + sv[0] + vlane, *vl1 = smem + sv[1] + vlane;
     if (held)                                    // (S^T goes unused where !vis)
-      products(std::true_type{}, st, pb, kl, vl);
+      products(std::true_type{}, st, pb, kl, vl, vl1);
     else if (vis)
-      products(std::false_type{}, st, pb, kl, vl);
+      products(std::false_type{}, st, pb, kl, vl, vl1);
     wait_loads();                                // tile it + 1, issued a phase ago
     if (it == n_it) break;
     phase_end();
     // ---- softmax of tile it
     if (it + 2 < n_it) issue_loads(it + 2, smem + (so >= 2 * SB ? so - 2 * SB : so + 2 * SB));
     held = vis;
+    sv[0] = so;
+    sv[1] = so + P::STAGE;
     if (vis) {
       if (!whole) {
         int s0, se;
         tile_range(i_lo + it, &s0, &se);
         mask(st, s0, se);
+        // A block that no column of the wave sees has zero weights only; they meet
+        // the other block's values, so that what is not finite in it stays out.
+        if (U > 1 && !sees(s0, kKeys, se)) sv[0] = sv[1];
+        if (U > 1 && !sees(s0 + kKeys, kKeys, se)) sv[1] = sv[0];
       }
       raise(tile_max(st));
       tile_weights<U, F16>(st, pb, l, c2, m * c2 - pbias);
     }
-    so1 = so;
     so = so == (STAGES - 1) * SB ? 0 : so + SB;
     phase_end();
   }
@@ -1062,9 +1071,9 @@ void replay_attn(const ReplayAttnArgs a) {
     for (bool first = true;; first = false) {
       __builtin_amdgcn_s_waitcnt(0xc07f);        // as in prefill_attn
       if (held)
-        tile_products<D, NW, false, 1, true>(o, st, pb, qv, kl, vl);
+        tile_products<D, NW, false, 1, true>(o, st, pb, qv, kl, vl, vl);
       else if (vis)
-        tile_products<D, NW, false, 1, false>(o, st, pb, qv, kl, vl);
+        tile_products<D, NW, false, 1, false>(o, st, pb, qv, kl, vl, vl);
       held = false;
       if (first) {
         wait_loads();                            // tile it + 1, issued a phase ago

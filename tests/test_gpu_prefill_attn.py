@@ -184,3 +184,36 @@ def test_prefill128k_workload_sampled_rows():
     with timed("residency"):
         r.check_layer(0)
     r.free()
+
+
+# A zero weight times a value that is not finite is not zero, so such a value
+# reaches the columns of a wavefront (32 columns) that sees any key of its block
+# of 32 keys -- and no others: not the tokens before it, nor those whose window
+# has left it behind.
+@pytest.mark.parametrize("D,fmt", [(64, "bf16"), (128, "bf16"), (256, "bf16"), (64, "f16"), (128, "f16")])
+@pytest.mark.parametrize("at", [40, 70, 130, 191, 250])
+def test_reach_of_a_value_that_is_not_finite(D, fmt, at):
+    P0, N, H, G, S, WIN = 96, 192, 2, 4, 4, 40
+    pol = hwkv.policy_set(1, H, H * G, D, S, [WIN, 0], [[0, 1]])
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)
+    k, v, q = rnd(P0 + N, H, D), rnd(P0 + N, H, D), rnd(N, H * G, D)
+    outs = []
+    for bad in (False, True):
+        vb = v.clone()
+        if bad:
+            vb[at] = float("inf")
+        cache = hwkv.cache_alloc(pol, 1, P0 + N + 64, kv_format=fmt)
+        hwkv.prefill_write(cache, 0, 0, 0, k[:P0], vb[:P0])
+        ws = torch.empty(max(1, hwkv.prefill_attn_workspace_bytes(cache, N)), dtype=torch.uint8, device="cuda")
+        out = torch.empty(N, H * G, D, device="cuda")
+        hwkv.prefill_attn(cache, 0, 0, P0, q, k[P0:], vb[P0:], 0.1, out, ws=ws)
+        outs.append(out.reshape(N, H, G, D))
+        cache.free()
+    per = 32 // G                                    # tokens of a wavefront
+    lo = P0 + torch.arange(N, device="cuda") // per * per
+    before = at > lo + per - 1 + 31
+    past = at < lo + 1 - WIN - 31
+    for h, clean in ((0, before | past), (1, before)):
+        assert int(clean.sum()) >= (16 if at > 150 or h == 0 else 0)
+        assert torch.equal(outs[0][clean, h], outs[1][clean, h])
