@@ -199,15 +199,25 @@ __global__ __launch_bounds__(item_waves(D, G) * 64) void decode_item(ItemArgs a)
       // tile it would take them from the loads in flight)
       int q0 = 0;
       asm volatile("" : "+v"(q0));
-      float s[G];
+      // a head's logit is the sum of four partial ones, of a quarter of the channels
+      // each, as decode_split's waves hold them: one chain over all channels has
+      // about twice their rounding error (both opaque in every step, below)
+      float s[G], zsum[G];
 #pragma unroll
-      for (int g = 0; g < G; ++g) s[g] = 0.f;
+      for (int g = 0; g < G; ++g) s[g] = zsum[g] = 0.f;
       static_for<NC>([&](auto jc) {
         constexpr int q = decltype(jc)::value;
+        if constexpr (F != HWKV_KV_FP8_E4M3 && q > 0 && q % (NC / 4) == 0) {
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            zsum[g] += s[g];
+            s[g] = 0.f;
+          }
+        }
         // (opaque at each step, so that each issues its own loads: the
         // compiler would otherwise hoist a tile's loads and spill)
 #pragma unroll
-        for (int g = 0; g < G; ++g) asm volatile("" : "+v"(s[g]));
+        for (int g = 0; g < G; ++g) asm volatile("" : "+v"(s[g]), "+v"(zsum[g]));
         const Chunk x = buf[q % PF];
         issue(jc);
         const u32x4_t *q4 = reinterpret_cast<const u32x4_t *>(sm.q + q0) + q;
@@ -251,8 +261,8 @@ __global__ __launch_bounds__(item_waves(D, G) * 64) void decode_item(ItemArgs a)
       const bool valid = 64 * t + lane < nv;
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        const float z = valid ? s[g] * sm.qsc[g] : -INFINITY;
-        const float mn = fmaxf(m[g], wave_max(z));
+        const float x = zsum[g] + s[g], c = sm.qsc[g];
+        const float mn = fmaxf(m[g], wave_max(valid ? x * c : -INFINITY));
         if (mn > m[g]) {                         // uniform
           const float alpha = exp2f(m[g] - mn);
           l[g] *= alpha;
@@ -260,7 +270,8 @@ __global__ __launch_bounds__(item_waves(D, G) * 64) void decode_item(ItemArgs a)
           for (int e = 0; e < 8; ++e) acc[g][e] *= alpha;
           m[g] = mn;
         }
-        const float p = exp2f(z - mn);
+        // the logit enters unrounded: half an ulp of it is as much as the sums' error
+        const float p = valid ? exp2f(fmaf(x, c, -mn)) : 0.f;
         l[g] += p;
         pl[lane * PST + g] = p;
       }
