@@ -205,27 +205,19 @@ struct PrefillAttnArgs {
 
 // Keys per tile: 64, or 32 at head_dim 256 (four tiles fit LDS).
 __host__ __device__ constexpr int prefill_keys(int D) { return D > 128 ? 32 : 64; }
-// Where the cached key s of a block of 32 keys lies, under S sinks and window W
-// (0 = full): `first` is the slot of the block's first key, and offsets count
-// from the row of slot `base`, itself a 64-bit offset from the unit's start --
-// from the start they need not fit in 32 bits (the bf16 image of an fp8 unit
-// has up to 2^32 bytes).  A ring that wraps within the block has two bases.
-struct CachedRow {
-  int base;                      // first, or S past the ring's wrap
-  int k, v;                      // bytes past the K tile of base / the V row of base
-};
+// Slot of the cached position s under S sinks and window W (0 = full), and byte
+// offsets of a slot's first K chunk and V row from their unit's start, for 2-byte
+// elements.  They need 32 bits without a sign: a unit has less than 2^31 bytes as
+// stored, so the bf16 image of an fp8 unit, whole 64-slot tiles of 64 channels or
+// more, ends at kRowSpan at the latest.
+constexpr uint32_t kRowSpan = 0xffffffffu - 2 * kTile * 64 + 1;
 __host__ __device__ inline int cached_slot(int s, int S, int W) {
   return W == 0 || s < S ? s : S + (s - S) % W;
 }
-__host__ __device__ inline int64_t cached_base_k(int D, int base) {
-  return (int64_t)(base >> 6) * (kTile * D * 2);
+__host__ __device__ inline uint32_t cached_k(uint32_t D, uint32_t slot) {
+  return (slot >> 6) * (kTile * D * 2) + (slot & 63) * 16;
 }
-__host__ __device__ inline int64_t cached_base_v(int D, int base) { return (int64_t)base * (D * 2); }
-__host__ __device__ inline CachedRow cached_row(int D, int slot, int first, int S) {
-  const int base = slot >= first ? first : S;
-  return {base, ((slot >> 6) - (base >> 6)) * (kTile * D * 2) + (slot & 63) * 16,
-          (slot - base) * (D * 2)};
-}
+__host__ __device__ inline uint32_t cached_v(uint32_t D, uint32_t slot) { return slot * (D * 2); }
 // Tiles of KT keys of a column block whose tokens sit at positions [ta, tb],
 // under S sinks and window W (0 = full): the key ranges are [0, tb + 1) in
 // one, or the sinks [0, S) and the window's keys [ta + 1 - W, tb + 1) where

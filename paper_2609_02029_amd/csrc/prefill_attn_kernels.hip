@@ -145,17 +145,17 @@ __device__ __forceinline__ f32x16_t mfma16(u32x4_t a, u32x4_t b, f32x16_t c) {
 }
 
 // 16 bytes from global memory into the LDS block of the issuing instruction, at
-// a scalar base and 32-bit byte offsets (lane's and uniform), which count from
-// the first row that an instruction reads.  The descriptor spans 2^31 bytes; an
-// access is out of range, and reads as zero, where the lane's offset is at or
-// past the span less the uniform offset, so a lane offset of the span itself
-// always is.
-constexpr uint32_t kSpan = 0x80000000u;
-constexpr int kNoRow = (int)kSpan;
+// a scalar base and unsigned 32-bit byte offsets (lane's and uniform).  The
+// descriptor spans kRowSpan bytes, as many as the largest unit's K or V (the bf16
+// image of an fp8 unit) has; an access is out of range, and reads as zero, where
+// the lane's offset is at or past the span less the uniform offset, so an offset
+// past the span always is.
+constexpr uint32_t kNoRow = 0xfffff000u;
+static_assert(kNoRow >= kRowSpan, "no row lies there");
 typedef u32x4_t rsrc_t;
 __device__ __forceinline__ rsrc_t make_rsrc(const void *base) {
   const uint64_t u = (uint64_t)base;
-  return rsrc_t{(uint32_t)u, (uint32_t)(u >> 32) & 0xffffu, kSpan, 0x00020000u};
+  return rsrc_t{(uint32_t)u, (uint32_t)(u >> 32) & 0xffffu, kRowSpan, 0x00020000u};
 }
 __device__ __forceinline__ const uint8_t *scalar_ptr(const void *p) {
   const uint64_t u = (uint64_t)p;
@@ -167,8 +167,8 @@ __device__ __forceinline__ const uint8_t *scalar_ptr(const void *p) {
 // (wait_loads, then a barrier).  As a builtin it would make the compiler wait
 // for every load in flight before each transposing read of LDS, the next
 // tiles' loads among them, which are to stay in flight.
-__device__ __forceinline__ void b2lds(rsrc_t r, uint8_t *lds_block, int voffset,
-                                      int soffset) {
+__device__ __forceinline__ void b2lds(rsrc_t r, uint8_t *lds_block, uint32_t voffset,
+                                      uint32_t soffset) {
   asm volatile(
       "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(
           (uint32_t)(uintptr_t)(lds_void_t *)lds_block),
@@ -511,7 +511,7 @@ void prefill_attn(const PrefillAttnArgs a) {
   int kstep = 0, kper = 0, vstep = 0, kn = 0;
   int ko = 0, ko2 = 0, vo = 0;
   constexpr int TB = kTile * D * 2;                 // bytes of a K tile
-  auto put = [&](const uint8_t *kb, const uint8_t *vb, int ko, int vo, int kn, uint8_t *stage) {
+  auto put = [&](const uint8_t *kb, const uint8_t *vb, uint32_t ko, uint32_t vo, int kn, uint8_t *stage) {
     const rsrc_t kr = make_rsrc(scalar_ptr(kb)), vr = make_rsrc(scalar_ptr(vb));
     kn = __builtin_amdgcn_readfirstlane(kn);
     uint8_t *kl = stage + lblk * P::STAGE + ln * 1024;
@@ -593,15 +593,15 @@ void prefill_attn(const PrefillAttnArgs a) {
             put(reinterpret_cast<const uint8_t *>(kin + at),
                 reinterpret_cast<const uint8_t *>(vin + at), off, off, 32, stage);
         }
-        if (pto >= 0 && s0 >= ce) kb = kcb;         // no cached key: nothing is read
+        int sl = cached_slot(s, S, W);
+        if (pto >= 0) {
+          sl &= kPageTokens - 1;
+          if (s0 >= ce) kb = kcb;                   // no cached key: nothing is read
+        }
         const bool cached = s < ce;
-        const int sl = pto >= 0 ? sl0 + lkey : cached_slot(s, S, W);
-        const CachedRow cr = cached_row(D, sl, sl0, S);
-        const int ck = cached ? cr.k + half * 1024 : kNoRow, cv = cached ? cr.v + half * 16 : kNoRow;
-        if (!own && cr.base == sl0)
-          put(kb + cached_base_k(D, sl0), vb + cached_base_v(D, sl0), ck, cv, 2048, stage);
-        if (!own && cr.base != sl0)                 // past the ring's wrap
-          put(kb + cached_base_k(D, S), vb + cached_base_v(D, S), ck, cv, 2048, stage);
+        if (!own)
+          put(kb, vb, cached ? cached_k(D, sl) + half * 1024 : kNoRow,
+              cached ? cached_v(D, sl) + half * 16 : kNoRow, 2048, stage);
         return;
       }
     }
@@ -720,14 +720,12 @@ void prefill_attn(const PrefillAttnArgs a) {
     f1 = wave_live ? f1 - i_lo : f0;
   }
   const uint32_t fn = (uint32_t)max(f1 - f0, 0);
-  // whether any column of this wave sees a key of [s0, min(s0 + n, se))
-  auto sees = [&](int s0, int n, int se) {
-    return wave_live && s0 <= t_hi && !(W != 0 && s0 >= S && min(s0 + n, se) - 1 < t_lo + 1 - W);
-  };
-  auto visible = [&](int it) {                   // of tile it
+  // whether any column of this wave sees a key of tile it
+  auto visible = [&](int it) {
     int s0, se;
     tile_range(i_lo + it, &s0, &se);
-    return sees(s0, KT, se);
+    const int slast = min(s0 + KT, se) - 1;
+    return wave_live && s0 <= t_hi && !(W != 0 && s0 >= S && slast < t_lo + 1 - W);
   };
   constexpr int SB = U * P::STAGE;               // bytes of a stage
 #pragma unroll 1
@@ -749,13 +747,13 @@ void prefill_attn(const PrefillAttnArgs a) {
   u32x4_t pb[2 * U];                             // the weights of the tile, packed
   bool held = false;                             // pb holds weights to add
   int so = 0;                                    // LDS offset of tile it
-  int sv[2] = {0, 0};                            // and of the blocks whose values pb weighs
+  int sv = 0, dv = 0;                            // and of the values pb weighs: first block, second
   for (int it = 0;; ++it) {
     // ---- products: S^T of tile it, then V^T P^T of tile it - 1
     const bool whole = (uint32_t)(it - f0) < fn;
     const bool vis = it < n_it && (whole || visible(it));
     __builtin_amdgcn_s_waitcnt(0xc07f);          // no scalar load outstanding: LDS waits can count
-    const uint8_t *kl = smem + so + klane, *vl = smem + sv[0] + vlane, *vl1 = smem + sv[1] + vlane;
+    const uint8_t *kl = smem + so + klane, *vl = smem + sv + vlane, *vl1 = vl + dv;
     if (held)                                    // (S^T goes unused where !vis)
       products(std::true_type{}, st, pb, kl, vl, vl1);
     else if (vis)
@@ -766,17 +764,23 @@ void prefill_attn(const PrefillAttnArgs a) {
     // ---- softmax of tile it
     if (it + 2 < n_it) issue_loads(it + 2, smem + (so >= 2 * SB ? so - 2 * SB : so + 2 * SB));
     held = vis;
-    sv[0] = so;
-    sv[1] = so + P::STAGE;
+    sv = so;
+    dv = P::STAGE;
     if (vis) {
       if (!whole) {
         int s0, se;
         tile_range(i_lo + it, &s0, &se);
         mask(st, s0, se);
-        // A block that no column of the wave sees has zero weights only; they meet
-        // the other block's values, so that what is not finite in it stays out.
-        if (U > 1 && !sees(s0, kKeys, se)) sv[0] = sv[1];
-        if (U > 1 && !sees(s0 + kKeys, kKeys, se)) sv[1] = sv[0];
+        // A block that no column of the wave sees (of a tile that it sees: the second
+        // past its tokens, or the first below its windows) has zero weights only;
+        // they meet the other block's values, so that what is not finite in it
+        // stays out.
+        if (U > 1 && s0 + kKeys > t_hi) {
+          dv = 0;
+        } else if (U > 1 && W != 0 && s0 >= S && s0 + kKeys <= t_lo + 1 - W) {
+          sv = so + P::STAGE;
+          dv = 0;
+        }
       }
       raise(tile_max(st));
       tile_weights<U, F16>(st, pb, l, c2, m * c2 - pbias);

@@ -11,17 +11,14 @@ from paper_2609_02029_amd import build
 
 SOURCE = """
 #include "hwkv_internal.h"
-extern "C" void rows(int D, int s0, int S, int W, int paged, int64_t *k, int64_t *v, int64_t *at) {
-  const int first = paged ? s0 % hwkv::kPageTokens : hwkv::cached_slot(s0, S, W);
+extern "C" void rows(int D, int s0, int S, int W, uint32_t *k, uint32_t *v) {
   for (int i = 0; i < 32; ++i) {
-    const int slot = paged ? first + i : hwkv::cached_slot(s0 + i, S, W);
-    const hwkv::CachedRow r = hwkv::cached_row(D, slot, first, S);
-    k[i] = hwkv::cached_base_k(D, r.base) + r.k;
-    v[i] = hwkv::cached_base_v(D, r.base) + r.v;
-    at[i] = r.k < r.v ? r.v : r.k;
-    if (r.k < 0 || r.v < 0) at[i] = -1;
+    const int slot = hwkv::cached_slot(s0 + i, S, W);
+    k[i] = hwkv::cached_k(D, slot);
+    v[i] = hwkv::cached_v(D, slot);
   }
 }
+extern "C" uint32_t span() { return hwkv::kRowSpan; }
 """
 
 
@@ -34,12 +31,14 @@ def rows(tmp_path_factory):
     subprocess.run([build.HIPCC, *build.CFLAGS, "-O1", "--offload-host-only", "-shared",
                     str(d / "rows.hip"), "-o", str(d / "rows.so")], check=True, capture_output=True)
     lib = ctypes.CDLL(str(d / "rows.so"))
+    lib.span.restype = ctypes.c_uint32
 
-    def call(D, s0, S, W, paged=0):
-        out = [(ctypes.c_int64 * 32)() for _ in range(3)]
-        lib.rows(D, s0, S, W, paged, *out)
+    def call(D, s0, S, W):
+        out = [(ctypes.c_uint32 * 32)() for _ in range(2)]
+        lib.rows(D, s0, S, W, *out)
         return [list(x) for x in out]
 
+    call.span = lib.span()
     return call
 
 
@@ -52,7 +51,7 @@ def layout(D, slot):
 def test_offsets_at_any_slot(rows, D):
     top = (2 ** 31 - 1) // D // 64 * 64               # slots of the largest fp8 unit
     half = 2 ** 30 // D                               # its 2^31-byte mark as bf16
-    assert top * D * 2 > 2 ** 31
+    assert 2 ** 31 < top * D * 2 <= rows.span
     for S, W in [(0, 0), (4, 0), (0, half + 1), (33, top - 40), (4, 500), (3, 1), (0, 31), (70, 33)]:
         cap = S + W if W else top
         starts = {0, 1, 32, S, max(0, S - 31), half - 32, half - 16, half, half + 32, cap - 40, cap - 32, cap - 5,
@@ -60,16 +59,10 @@ def test_offsets_at_any_slot(rows, D):
         for s0 in sorted(starts):
             if s0 < 0 or s0 + 32 > (top if W == 0 else 2 * top):
                 continue
-            k, v, at = rows(D, s0, S, W)
+            k, v = rows(D, s0, S, W)
             for i in range(32):
                 s = s0 + i
                 slot = s if W == 0 or s < S else S + (s - S) % W
                 assert (k[i], v[i]) == layout(D, slot), (S, W, s0, i)
-                # small enough for the kernel's 32-bit offsets
-                assert 0 <= at[i] < 2 * 64 * D * 2, (S, W, s0, i)
-
-
-def test_offsets_within_a_page(rows):
-    for s0 in (0, 32, 224, 256, 4_000_032):
-        k, v, _ = rows(128, s0, 4, 0, 1)
-        assert list(zip(k, v)) == [layout(128, s0 % 256 + i) for i in range(32)]
+                # the last loads of the row stay within the descriptor's span
+                assert k[i] + (D // 8 - 1) * 1024 + 16 <= rows.span and v[i] + D * 2 <= rows.span
