@@ -265,11 +265,7 @@ int hwkv_prefill_write(hwkv_cache *cache, int32_t layer, int32_t seq,
  * ECAPACITY if pos0 + n_tokens > max_ctx; EINVAL on bad indices, null
  * pointers, a non-finite or non-positive scale, or a cache whose format is
  * not bf16 (hwkv_prefill_attn_ws takes every format); n_tokens == 0 is a
- * no-op.
- * A launch that would leave CUs idle splits its keys; the partials go into
- * device buffers that the library keeps, at most two per device, while a cache
- * that used them lives.  Calls of any stream or thread may share them; without
- * one at hand, or while `stream` is captured, the keys are not split. */
+ * no-op. */
 int hwkv_prefill_attn(hwkv_cache *cache, int32_t layer, int32_t seq,
                       int64_t pos0, int64_t n_tokens, const void *q,
                       const void *k, const void *v, float scale, void *out,
@@ -308,6 +304,29 @@ int hwkv_prefill_attn_ws(hwkv_cache *cache, int32_t layer, int32_t seq,
                          int64_t pos0, int64_t n_tokens, const void *q,
                          const void *k, const void *v, float scale, void *out,
                          void *ws, size_t ws_bytes, void *stream);
+
+/* Device bytes of the partials with which hwkv_prefill_attn_split splits the
+ * keys of a chunk [pos0, pos0 + n_tokens) of `layer`; 0 where it would not
+ * split them.  At most 2 x CUs x 256 x (head_dim + 2) x 4 (135 MB on 256 CUs at
+ * head_dim 256).  EINVAL on a bad layer, a negative position or count or null
+ * pointers, ECAPACITY past max_ctx. */
+int hwkv_prefill_attn_split_bytes(const hwkv_cache *cache, int32_t layer,
+                                  int64_t pos0, int64_t n_tokens, size_t *bytes);
+
+/* hwkv_prefill_attn_ws that may split its keys over more workgroups, where the
+ * chunk alone (few tokens over many keys) would leave CUs idle.
+ *   parts, part_bytes  device buffer of >= hwkv_prefill_attn_split_bytes for
+ *                      the call, 16-byte aligned, used until the call's work on
+ *                      `stream` is done; too small or NULL: the keys are not
+ *                      split
+ * A split adds the keys in another order, and rounds the softmax weights under
+ * another shift: outputs differ from the unsplit call's within its accuracy,
+ * and are the same in every split call of the same arguments. */
+int hwkv_prefill_attn_split(hwkv_cache *cache, int32_t layer, int32_t seq,
+                            int64_t pos0, int64_t n_tokens, const void *q,
+                            const void *k, const void *v, float scale, void *out,
+                            void *ws, size_t ws_bytes, void *parts,
+                            size_t part_bytes, void *stream);
 
 /* Append one token to every sequence of `layer`: token n_b of sequence b
  * goes to slot(n_b) of each unit (once n_b >= S + w this overwrites token

@@ -56,7 +56,6 @@ struct hwkv_cache {
   size_t bytes = 0;
   bool owned = false;
   size_t ws_bytes = 0;
-  int device = -1;               // device whose prefill partials it keeps alive, or -1
   // kernel timing (profiling): events recorded by decode calls
   bool timing = false;
   std::vector<hipEvent_t> ev_pool;   // created events, reused
@@ -227,9 +226,6 @@ int alloc_impl(hwkv_cache **out, const hwkv_policy *p, int32_t batch, int64_t ma
                int32_t kv_format, const float *k_scale, const float *v_scale, bool paged,
                int64_t n_pages, void *dev_buf, size_t buf_bytes);
 
-// Counts the caches of a device, which keep its prefill partials alive.
-void prefill_pool_cache(hwkv_cache *c, int step);
-
 int64_t group_size(const hwkv_policy &p) { return p.n_q_heads / p.n_kv_heads; }
 
 // 64-slot tiles of an item with n_valid rows.
@@ -388,9 +384,6 @@ struct PrefillPlan {
   int64_t wgs = 0;
 };
 
-// Workgroups whose partials a cache keeps room for: two per CU.
-int64_t prefill_split_limit() { return 2 * (int64_t)hwkv::device_cu_count(); }
-
 // Splits the keys of a launch of nb column blocks per head over more
 // workgroups where the blocks alone leave CUs idle (few tokens, or one head
 // with far more keys than the others).  One workgroup runs per CU, so a
@@ -398,23 +391,26 @@ int64_t prefill_split_limit() { return 2 * (int64_t)hwkv::device_cu_count(); }
 // the CUs, whichever is more; splits of T tiles run in k rounds of at most
 // one per CU, each with its own start and its partial to write and merge
 // (kSplitCost tiles a round), and the merge launch and the event after it take
-// about as long as kMergeCost tiles (8 us of 1.6 us).  tiles: per head, the tiles of its first column
-// block and a bound of every block's.
-constexpr int64_t kSplitCost = 6, kMergeCost = 5, kSplitLeast = 4;
-PrefillPlan plan_prefill(const std::vector<std::pair<int64_t, int64_t>> &tiles, int64_t nb) {
+// about as long as kMergeCost tiles (8 us of 1.6 us).
+constexpr int64_t kSplitCost = 6, kMergeCost = 5, kSplitLeast = 4, kSplitRounds = 2;
+// Tiles of a head's first column block and a bound of every block's.
+struct HeadTiles {
+  int64_t first, most;
+};
+PrefillPlan plan_prefill(const HeadTiles *tiles, int32_t n_heads, int64_t nb) {
   PrefillPlan p;
-  p.wgs = nb * (int64_t)tiles.size();
+  p.wgs = nb * n_heads;
   const int64_t cus = hwkv::device_cu_count();
   int64_t total = 0, longest = 1;
-  for (const auto &t : tiles) {
-    total += nb * (t.first + t.second) / 2;
-    longest = std::max(longest, t.second);
+  for (int32_t h = 0; h < n_heads; ++h) {
+    total += nb * (tiles[h].first + tiles[h].most) / 2;
+    longest = std::max(longest, tiles[h].most);
   }
   int64_t best = std::max(longest, (total + cus - 1) / cus);
-  for (int64_t k = 1; k * cus <= prefill_split_limit(); ++k) {
+  for (int64_t k = 1; k <= kSplitRounds; ++k) {
     auto count = [&](int64_t T) {
       int64_t n = 0;
-      for (const auto &t : tiles) n += nb * ((t.second + T - 1) / T);
+      for (int32_t h = 0; h < n_heads; ++h) n += nb * ((tiles[h].most + T - 1) / T);
       return n;
     };
     int64_t T = std::max(kSplitLeast, (total + k * cus - 1) / (k * cus));
@@ -429,124 +425,32 @@ PrefillPlan plan_prefill(const std::vector<std::pair<int64_t, int64_t>> &tiles, 
   return p;
 }
 
-// Split partials of prefill attention.  Each device has at most two buffers,
-// allocated by the first calls that split their keys and shared by the
-// device's caches; they are freed with the last of these.  A call holds one
-// buffer while it enqueues its work and leaves an event behind it, which the
-// buffer's next user waits for on its own stream, so that calls on several
-// streams and host threads never meet in one buffer.
-struct PrefillPartials {
-  float *ptr = nullptr;
-  size_t bytes = 0;
-  hipEvent_t done = nullptr;     // after the last use
-  hipStream_t stream = nullptr;  // of the last use
-  bool used = false, busy = false;
-};
-struct PrefillPool {
-  std::vector<PrefillPartials *> bufs;
-  int caches = 0;                // caches alive on the device
-};
-constexpr size_t kPrefillBuffers = 2;
-std::mutex g_pf_mu;
-// never destroyed: a cache may be freed while the process ends
-std::map<int, PrefillPool> &prefill_pools() {
-  static auto *pools = new std::map<int, PrefillPool>;
-  return *pools;
+// The tiles of one head (window W, 0 = full) of a chunk: of its first column
+// block, and of its longest: the last one of a full unit; for a window (whose
+// last block may be short), the sinks' tiles and those of the window and a
+// block's span of tokens, which bounds both forms of the key ranges
+// (prefill_tiles).
+HeadTiles head_tiles(const hwkv_policy &p, int64_t W, int64_t pos0, int64_t n_tokens) {
+  const int64_t G = group_size(p), KT = hwkv::prefill_keys(p.head_dim), S = p.n_sinks;
+  const int64_t per = hwkv::prefill_attn_columns_per_block(), span = (per + G - 2) / G;
+  const int64_t first = hwkv::prefill_tiles(
+      (int)KT, (int)pos0, (int)(pos0 + (std::min(per, n_tokens * G) - 1) / G), (int)S, (int)W);
+  const int64_t all = (pos0 + n_tokens + KT - 1) / KT, sinks = (S + KT - 1) / KT;
+  return {first, W == 0 ? all : std::min(sinks + (W + span - 1) / KT + 1, sinks + all)};
 }
 
-// Device memory calls are allowed while another thread captures a graph.
-struct RelaxedCapture {
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-};
-
-void free_partials(PrefillPartials *b) {
-  RelaxedCapture relaxed;
-  if (b->ptr) (void)hipFree(b->ptr);
-  if (b->done) (void)hipEventDestroy(b->done);
-  (void)hipGetLastError();
-  delete b;
+// Bytes of the partials of wgs workgroups: acc rows, then (m, l) pairs.
+size_t prefill_part_bytes(const hwkv_policy &p, int64_t wgs) {
+  return (size_t)wgs * (size_t)hwkv::prefill_attn_columns_per_block() * (size_t)(p.head_dim + 2) *
+         sizeof(float);
 }
 
-PrefillPartials *new_partials(size_t bytes) {
-  PrefillPartials *b = new (std::nothrow) PrefillPartials;
-  if (!b) return nullptr;
-  RelaxedCapture relaxed;
-  void *ptr = nullptr;
-  if (hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) b->done = nullptr;
-  if (b->done && hipMalloc(&ptr, bytes) == hipSuccess) {
-    b->ptr = static_cast<float *>(ptr);
-    b->bytes = bytes;
-    return b;
-  }
-  free_partials(b);
-  return nullptr;
-}
-
-// A cache of the current device begins (+1) or ends (-1).
-void prefill_pool_cache(hwkv_cache *c, int step) {
-  if (step > 0 && hipGetDevice(&c->device) != hipSuccess) {
-    (void)hipGetLastError();
-    c->device = -1;
-  }
-  if (c->device < 0) return;
-  std::vector<PrefillPartials *> dead;
-  try {
-    std::lock_guard<std::mutex> lock(g_pf_mu);
-    PrefillPool &p = prefill_pools()[c->device];
-    p.bufs.reserve(kPrefillBuffers);
-    p.caches += step;
-    if (p.caches == 0) dead.swap(p.bufs);
-  } catch (const std::bad_alloc &) {
-    c->device = -1;              // (a beginning cache: its calls run unsplit)
-  }
-  for (PrefillPartials *b : dead) free_partials(b);
-}
-
-// A buffer for the partials of wgs workgroups of a call on st, or null if the
-// call has to run unsplit: a stream under capture (a graph's replays are not
-// ordered with other calls' use of a buffer), no memory, or both buffers held
-// by other threads.
-PrefillPartials *take_partials(const hwkv_cache *c, int64_t wgs, hipStream_t st) {
-  int dev = -1;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (wgs > prefill_split_limit() || hipGetDevice(&dev) != hipSuccess || dev != c->device ||
-      hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  const size_t bytes = (size_t)prefill_split_limit() *
-                       (size_t)hwkv::prefill_attn_columns_per_block() * (c->pol.head_dim + 2) * 4;
-  std::lock_guard<std::mutex> lock(g_pf_mu);
-  PrefillPool &p = prefill_pools()[dev];   // made by the cache; bufs has its room
-  PrefillPartials *best = nullptr, *small = nullptr;
-  for (PrefillPartials *b : p.bufs) {
-    if (b->busy) continue;
-    if (b->bytes < bytes)
-      small = b;
-    else if (!best || b->stream == st)
-      best = b;
-  }
-  // a stream of its own gets a buffer of its own while there are any
-  if (!best || (best->used && best->stream != st)) {
-    if (!best && small && p.bufs.size() == kPrefillBuffers) {
-      p.bufs.erase(std::find(p.bufs.begin(), p.bufs.end(), small));
-      free_partials(small);      // (waits for the device)
-    }
-    if (p.bufs.size() < kPrefillBuffers)
-      if (PrefillPartials *b = new_partials(bytes)) {
-        p.bufs.push_back(b);
-        best = b;
-      }
-  }
-  if (best) best->busy = true;
-  return best;
-}
-
+// parts: room for split partials, or null.  The keys are split where that pays
+// and the partials fit, which the arguments alone decide.
 int prefill_attn_impl(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
                       int64_t n_tokens, const void *q, const void *k, const void *v,
-                      float scale, void *out, void *ws, size_t ws_bytes, void *stream) {
+                      float scale, void *out, void *ws, size_t ws_bytes, void *parts,
+                      size_t part_bytes, void *stream) {
   if (!c) return fail(HWKV_EINVAL, "cache is null");
   // fp8: the units are staged as bf16 code values; fp8 and binary16: the
   // chunk's own keys and values are staged as the cache will store them
@@ -567,6 +471,8 @@ int prefill_attn_impl(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
   if (n_tokens == 0) return ok();
   if (!q || !k || !v || !out)
     return fail(HWKV_EINVAL, "q, k, v and out must be non-null");
+  if ((uintptr_t)parts % 16 != 0)
+    return fail(HWKV_EINVAL, "the partials must be 16-byte aligned");
   StageLayout SL;
   if (chunk_staged) {
     const size_t need = stage_layout(c, layer, n_tokens, &SL);
@@ -616,42 +522,25 @@ int prefill_attn_impl(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
   const int64_t nb = (cols + per - 1) / per;
   if (nb * H > (int64_t)INT32_MAX)
     return fail(HWKV_EINVAL, "n_tokens too large for one launch");
-  // key tiles of each head's first column block, and of its longest: the last
-  // one of a full unit; for a window (whose last block may be short), the
-  // sinks' tiles and those of the window and a block's span of tokens, which
-  // bounds both forms of the key ranges (prefill_tiles)
-  std::vector<std::pair<int64_t, int64_t>> tiles(H);
-  const int64_t span = (per + G - 2) / G;
-  for (int32_t r = 0; r < H; ++r) {
-    const int64_t W = a.head[r].window, KT = hwkv::prefill_keys((int)D);
-    const int64_t first = hwkv::prefill_tiles(
-        (int)KT, (int)pos0, (int)(pos0 + (std::min(per, cols) - 1) / G), p.n_sinks, (int)W);
-    const int64_t all = (p1 + KT - 1) / KT, sinks = (p.n_sinks + KT - 1) / KT;
-    tiles[r] = {first, W == 0 ? all : std::min(sinks + (W + span - 1) / KT + 1, sinks + all)};
+  HeadTiles tiles[hwkv::kMaxItems];
+  PrefillPlan plan;
+  if (parts) {
+    for (int32_t r = 0; r < H; ++r) tiles[r] = head_tiles(p, a.head[r].window, pos0, n_tokens);
+    plan = plan_prefill(tiles, H, nb);
+    a.split = plan.wgs > nb * H && prefill_part_bytes(p, plan.wgs) <= part_bytes;
   }
-  PrefillPlan plan = plan_prefill(tiles, nb);
-  PrefillPartials *parts = plan.wgs > nb * H ? take_partials(c, plan.wgs, st) : nullptr;
-  struct Release {                // on every way out
-    PrefillPartials *b;
-    ~Release() {
-      if (!b) return;
-      std::lock_guard<std::mutex> lock(g_pf_mu);
-      b->busy = false;
-    }
-  } release{parts};
-  if (!parts) plan = PrefillPlan{};
+  if (!a.split) plan = PrefillPlan{};
   a.tiles_per_split = (int32_t)plan.tiles_per_split;
   int64_t begin = 0;
   for (int32_t r = 0; r < H; ++r) {
     a.head[r].wg_begin = (int32_t)begin;
-    begin += nb * ((tiles[r].second + plan.tiles_per_split - 1) / plan.tiles_per_split);
+    begin += a.split ? nb * ((tiles[r].most + plan.tiles_per_split - 1) / plan.tiles_per_split) : nb;
   }
   a.n_wgs = (int32_t)begin;
-  a.split = parts != nullptr;
   for (int32_t r = H; r < hwkv::kMaxItems; ++r) a.head[r].wg_begin = INT32_MAX;
-  if (parts) {
-    a.part_acc = parts->ptr;
-    a.part_ml = parts->ptr + (size_t)prefill_split_limit() * per * p.head_dim;
+  if (a.split) {
+    a.part_acc = static_cast<float *>(parts);
+    a.part_ml = a.part_acc + (size_t)begin * per * p.head_dim;
   }
   uint16_t *img = static_cast<uint16_t *>(ws);
   if (staged) {
@@ -720,19 +609,10 @@ int prefill_attn_impl(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
   a.n_sinks = p.n_sinks;
   a.n_col_blocks = (int32_t)nb;
   a.scale_log2 = scale * 1.4426950408889634f;
-  int rc = HWKV_OK;
-  if (parts && parts->used)
-    rc = check_device(hipStreamWaitEvent(st, parts->done, 0), "hipStreamWaitEvent");
-  if (rc == HWKV_OK)
-    rc = check_device(hwkv::launch_prefill_attn(p.head_dim, c->fmt == HWKV_KV_F16, a, st),
-                      "prefill_attn launch");
-  if (rc == HWKV_OK && parts) {
+  int rc = check_device(hwkv::launch_prefill_attn(p.head_dim, c->fmt == HWKV_KV_F16, a, st),
+                        "prefill_attn launch");
+  if (rc == HWKV_OK && a.split)
     rc = check_device(hwkv::launch_prefill_merge(p.head_dim, a, st), "prefill_merge launch");
-    const int rr = check_device(hipEventRecord(parts->done, st), "hipEventRecord");
-    parts->used = true;
-    parts->stream = st;
-    if (rc == HWKV_OK) rc = rr;
-  }
   return rc == HWKV_OK ? ok() : HWKV_EDEVICE;
 }
 
@@ -1284,7 +1164,6 @@ int alloc_impl(hwkv_cache **out, const hwkv_policy *p, int32_t batch, int64_t ma
     delete c;
     return fail(HWKV_ENOMEM, "host allocation failed");
   }
-  prefill_pool_cache(c, +1);
   *out = c;
   return ok();
 }
@@ -1297,7 +1176,6 @@ int hwkv_cache_free(hwkv_cache *c) {
   if (!c) return ok();
   int rc = HWKV_OK;
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
-  prefill_pool_cache(c, -1);
   if (c->owned && c->base) {
     hipError_t e = hipFree(c->base);
     if (e != hipSuccess) rc = check_device(e, "hipFree");
@@ -1467,7 +1345,7 @@ int hwkv_prefill_attn(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
     return fail(HWKV_EINVAL, "prefill attention needs a bf16 cache here "
                              "(hwkv_prefill_attn_ws takes fp8 and binary16 caches)");
   return prefill_attn_impl(c, layer, seq, pos0, n_tokens, q, k, v, scale, out,
-                           nullptr, 0, stream);
+                           nullptr, 0, nullptr, 0, stream);
 }
 
 int hwkv_prefill_attn_workspace_bytes(const hwkv_cache *c, int64_t n_tokens,
@@ -1486,7 +1364,36 @@ int hwkv_prefill_attn_ws(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0
                          const void *v, float scale, void *out, void *ws,
                          size_t ws_bytes, void *stream) {
   return prefill_attn_impl(c, layer, seq, pos0, n_tokens, q, k, v, scale, out, ws,
-                           ws_bytes, stream);
+                           ws_bytes, nullptr, 0, stream);
+}
+
+int hwkv_prefill_attn_split_bytes(const hwkv_cache *c, int32_t layer, int64_t pos0,
+                                  int64_t n_tokens, size_t *bytes) {
+  if (!c || !bytes) return fail(HWKV_EINVAL, "null argument");
+  const hwkv_policy &p = c->pol;
+  if (layer < 0 || layer >= p.n_layers) return fail(HWKV_EINVAL, "layer out of range");
+  if (pos0 < 0 || n_tokens < 0) return fail(HWKV_EINVAL, "pos0 and n_tokens must be >= 0");
+  if (pos0 > c->max_ctx || n_tokens > c->max_ctx - pos0)
+    return fail(HWKV_ECAPACITY, "prefill past max_ctx");
+  *bytes = 0;
+  if (n_tokens == 0) return ok();
+  const int64_t per = hwkv::prefill_attn_columns_per_block();
+  const int64_t nb = (n_tokens * group_size(p) + per - 1) / per;
+  HeadTiles tiles[hwkv::kMaxItems];
+  for (int32_t h = 0; h < p.n_kv_heads; ++h)
+    tiles[h] = head_tiles(p, c->window[layer * p.n_kv_heads + h], pos0, n_tokens);
+  const PrefillPlan plan = plan_prefill(tiles, p.n_kv_heads, nb);
+  if (plan.wgs > nb * p.n_kv_heads) *bytes = prefill_part_bytes(p, plan.wgs);
+  return ok();
+}
+
+int hwkv_prefill_attn_split(hwkv_cache *c, int32_t layer, int32_t seq, int64_t pos0,
+                            int64_t n_tokens, const void *q, const void *k,
+                            const void *v, float scale, void *out, void *ws,
+                            size_t ws_bytes, void *parts, size_t part_bytes,
+                            void *stream) {
+  return prefill_attn_impl(c, layer, seq, pos0, n_tokens, q, k, v, scale, out, ws,
+                           ws_bytes, parts, part_bytes, stream);
 }
 
 }  // extern "C"

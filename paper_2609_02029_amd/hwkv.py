@@ -29,7 +29,7 @@ if not os.path.exists(LIB_PATH):
 # torch owns device memory and streams: load it (and the HIP runtime it
 # initialises) before the library, so both use that one runtime whatever the
 # caller's import order.
-import torch  # noqa: E402,F401
+import torch  # noqa: E402
 
 _lib = ctypes.CDLL(LIB_PATH)
 
@@ -64,6 +64,9 @@ SYMBOLS = {
     "hwkv_prefill_attn_workspace_bytes": ([_vp, _i64, _P(_sz)], ctypes.c_int),
     "hwkv_prefill_attn_ws": ([_vp, _i32, _i32, _i64, _i64, _vp, _vp, _vp, ctypes.c_float, _vp,
                               _vp, _sz, _vp], ctypes.c_int),
+    "hwkv_prefill_attn_split_bytes": ([_vp, _i32, _i64, _i64, _P(_sz)], ctypes.c_int),
+    "hwkv_prefill_attn_split": ([_vp, _i32, _i32, _i64, _i64, _vp, _vp, _vp, ctypes.c_float, _vp,
+                                 _vp, _sz, _vp, _sz, _vp], ctypes.c_int),
     "hwkv_append": ([_vp, _i32, _vp, _vp, _vp], ctypes.c_int),
     "hwkv_decode_workspace_bytes": ([_vp, _P(_sz)], ctypes.c_int),
     "hwkv_decode_attn": ([_vp, _i32, _vp, _flt, _vp, _vp, _sz, _vp], ctypes.c_int),
@@ -337,11 +340,46 @@ def prefill_attn_workspace_bytes(cache, n_tokens):
     return r.value
 
 
-def prefill_attn(cache, layer, seq, pos0, q, k, v, scale, out, ws=None, stream=None):
+def prefill_attn_split_bytes(cache, layer, pos0, n_tokens):
+    """Bytes of the ``parts`` with which ``prefill_attn`` splits the keys of this
+    chunk; 0 where it would not."""
+    r = _sz()
+    _check(_lib.hwkv_prefill_attn_split_bytes(cache.handle, layer, pos0, n_tokens,
+                                              ctypes.byref(r)))
+    return r.value
+
+
+# Keys up to which no chunk is split: the least cost of a split launch is that of
+# 15 key tiles, of at least 32 keys each.
+_SPLIT_KEYS = 15 * 32
+
+
+def _new_parts(nbytes, stream, device):
+    """A buffer for split partials, taken and given back on ``stream`` like any
+    temporary tensor; None if memory is short, or under stream capture (whose
+    replays would outlive the buffer)."""
+    try:
+        if stream is not None:
+            if isinstance(stream, int):
+                stream = (torch.cuda.ExternalStream(stream, device=device) if stream
+                          else torch.cuda.default_stream(device))
+            with torch.cuda.stream(stream):
+                return _new_parts(nbytes, None, device)
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except RuntimeError:
+        return None
+
+
+def prefill_attn(cache, layer, seq, pos0, q, k, v, scale, out, ws=None, stream=None, parts=None):
     """``q``: bf16 [n_tokens, n_q_heads, head_dim]; ``k``, ``v``: bf16
     [n_tokens, n_kv_heads, head_dim]; ``out``: fp32 like ``q`` (device).
     ``ws``: uint8 device workspace (hwkv_prefill_attn_ws; needed by fp8
-    caches, see prefill_attn_workspace_bytes)."""
+    caches, see prefill_attn_workspace_bytes).  ``parts``: uint8 device buffer
+    for split partials (hwkv_prefill_attn_split, see prefill_attn_split_bytes);
+    without one the call takes a temporary tensor, or does not split its keys
+    where it cannot: under stream capture, or if memory is short."""
     n = q.shape[0]
     if tuple(q.shape) != (n, cache.n_q_heads, cache.head_dim):
         raise ValueError("q must be [n_tokens, n_q_heads, head_dim]")
@@ -349,17 +387,24 @@ def prefill_attn(cache, layer, seq, pos0, q, k, v, scale, out, ws=None, stream=N
         raise ValueError("k and v must be [n_tokens, n_kv_heads, head_dim]")
     if tuple(out.shape) != tuple(q.shape):
         raise ValueError("out must be [n_tokens, n_q_heads, head_dim]")
-    if ws is None:
-        _check(_lib.hwkv_prefill_attn(cache.handle, layer, seq, pos0, n,
-                                      _dev(q, "bfloat16", "q"), _dev(k, "bfloat16", "k"),
-                                      _dev(v, "bfloat16", "v"), float(scale),
-                                      _dev(out, "float32", "out"), _stream(stream)))
+    args = (cache.handle, layer, seq, pos0, n, _dev(q, "bfloat16", "q"), _dev(k, "bfloat16", "k"),
+            _dev(v, "bfloat16", "v"), float(scale), _dev(out, "float32", "out"))
+    if (parts is None and pos0 + n > _SPLIT_KEYS
+            and (ws is not None or getattr(cache, "kv_format", "bf16") == "bf16")):
+        r = _sz()       # (an error is the call's to report)
+        rc = _lib.hwkv_prefill_attn_split_bytes(cache.handle, layer, pos0, n, ctypes.byref(r))
+        if rc == OK and r.value:
+            parts = _new_parts(r.value, stream, q.device)
+    if parts is not None:
+        _check(_lib.hwkv_prefill_attn_split(*args, _dev(ws, "uint8", "ws"),
+                                            0 if ws is None else ws.numel(),
+                                            _dev(parts, "uint8", "parts"), parts.numel(),
+                                            _stream(stream)))
+    elif ws is None:
+        _check(_lib.hwkv_prefill_attn(*args, _stream(stream)))
     else:
-        _check(_lib.hwkv_prefill_attn_ws(cache.handle, layer, seq, pos0, n,
-                                         _dev(q, "bfloat16", "q"), _dev(k, "bfloat16", "k"),
-                                         _dev(v, "bfloat16", "v"), float(scale),
-                                         _dev(out, "float32", "out"), _dev(ws, "uint8", "ws"),
-                                         ws.numel(), _stream(stream)))
+        _check(_lib.hwkv_prefill_attn_ws(*args, _dev(ws, "uint8", "ws"), ws.numel(),
+                                         _stream(stream)))
 
 
 def append(cache, layer, k_new, v_new, stream=None):

@@ -1,7 +1,7 @@
 """Prefill attention whose keys are split over workgroups (few query tokens
-over many keys): parity at the edges of tiles, runs and splits, and the paths
-around the partials the cache keeps -- a captured call (which runs unsplit)
-and calls on several streams."""
+over many keys): parity at the edges of tiles, runs and splits, and the split
+partials -- a captured call without a buffer for them (which runs unsplit) and
+with one, calls on several streams, and no memory held after a call."""
 import numpy as np
 import pytest
 import torch
@@ -91,7 +91,92 @@ def test_captured_call_runs_unsplit_and_replays():
     r.free()
 
 
-def test_two_streams_share_the_partials():
+def test_captured_call_with_parts_splits():
+    r, ((q, k, v), _) = _pair(63)
+    out = torch.empty(2, 40, 8, 128, device="cuda")
+    nbytes = hwkv.prefill_attn_split_bytes(r.cache, 0, 4000, 40)
+    assert nbytes > 0
+    parts = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    call = lambda o, p: hwkv.prefill_attn(r.cache, 0, 0, 4000, q, k, v, r.scale, o, parts=p)
+    call(out[0], None)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call(out[1], parts)
+    for i in range(3):
+        parts.fill_(255)                  # NaN
+        out[1].fill_(float("nan"))
+        g.replay()
+        call(out[0], None)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1])
+    # too small a buffer: unsplit, as without one
+    small = torch.empty(2, 40, 8, 128, device="cuda")
+    call(small[0], parts[:nbytes - 16])
+    h = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(h):
+        call(small[1], None)
+    h.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(small[0], small[1]) and not torch.equal(small[0], out[0])
+    r.free()
+
+
+def _held():
+    """Device memory in use beside torch's own pool."""
+    torch.cuda.synchronize()
+    free, total = torch.cuda.mem_get_info()
+    return total - free - torch.cuda.memory_reserved()
+
+
+def test_a_split_call_keeps_no_memory():
+    r, chunks = _pair(64)
+    (q, k, v), _ = chunks
+    out = torch.empty(40, 8, 128, device="cuda")
+    g = torch.cuda.CUDAGraph()            # the kernels are loaded, none has split
+    with torch.cuda.graph(g):
+        hwkv.prefill_attn(r.cache, 0, 0, 4000, q, k, v, r.scale, out)
+    g.replay()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for s in streams:                     # their queues are made
+        with torch.cuda.stream(s):
+            torch.zeros(1 << 20, device="cuda")
+    before, used = _held(), torch.cuda.memory_allocated()
+    for s in (None, streams[0], streams[1], streams[2].cuda_stream):
+        hwkv.prefill_attn(r.cache, 0, 0, 4000, q, k, v, r.scale, out, stream=s)
+    assert _held() - before < (1 << 22)
+    assert torch.cuda.memory_allocated() == used
+    r.free()
+
+
+# Calls of four streams in flight at once, over caches of two head dims (partials
+# of two sizes): each has the result of a call alone.
+def test_many_streams_at_once():
+    jobs = []
+    for D, seed in ((64, 65), (256, 66), (64, 67), (256, 68)):
+        cfg = mini(head_dim=D, n_q_heads=8, level_windows=[700, 0], prompt=[6000], max_ctx=6100, seed=seed)
+        r = Run(cfg)
+        r.prefill(0, 0)
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        x = lambda h: torch.randn((40, h, D), generator=g, device="cuda").to(torch.bfloat16)
+        args = (r.cache, 0, 0, 6000, x(8), x(2), x(2), r.scale)
+        assert hwkv.prefill_attn_split_bytes(r.cache, 0, 6000, 40) > 0
+        lone = torch.empty(40, 8, D, device="cuda")
+        hwkv.prefill_attn(*args, lone)
+        torch.cuda.synchronize()
+        jobs.append((r, args, lone, torch.cuda.Stream(),
+                     [torch.full_like(lone, float("nan")) for _ in range(12)]))
+    torch.cuda.synchronize()
+    for i in range(12):
+        for r, args, lone, stream, outs in jobs:
+            hwkv.prefill_attn(*args, outs[i], stream=stream)
+    torch.cuda.synchronize()
+    for r, args, lone, stream, outs in jobs:
+        assert all(torch.equal(o, lone) for o in outs)
+        r.free()
+
+
+def test_two_streams_of_one_cache():
     r, chunks = _pair(62)
     lone = []
     for b, (q, k, v) in enumerate(chunks):

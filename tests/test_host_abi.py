@@ -216,6 +216,48 @@ def test_prefill_attn_host_errors(hw):
     L.hwkv_cache_free(h)
 
 
+def test_prefill_split_bytes(hw):
+    pol = hw.policy_set(2, 2, 8, 128, 4, [500, 0], [[0, 1], [0, 0]])
+    L, r = hw._lib, ctypes.c_size_t()
+    h1 = _fake_cache(hw, pol, 1, 40000)
+
+    def ask(layer, pos0, n, h=h1):
+        assert L.hwkv_prefill_attn_split_bytes(h, layer, pos0, n, ctypes.byref(r)) == hw.OK
+        return r.value
+
+    row = 256 * (128 + 2) * 4                      # partials of one workgroup
+    n = ask(0, 30000, 64)                          # one block of columns over 469 tiles
+    assert n > 0 and n % row == 0 and n // row > 2
+    assert ask(0, 0, 64) == 0 and ask(1, 30000, 64) == 0   # few keys
+    assert ask(0, 30000, 0) == 0
+    # a launch of at most 480 keys is never split, whatever its tokens
+    for d, g in ((64, 1), (128, 8), (256, 6)):
+        for h in (1, 2, 64):
+            p2 = hw.policy_set(1, h, h * g, d, 0, [100, 0], [[i % 2 for i in range(h)]])
+            h2 = _fake_cache(hw, p2, 1, 700)
+            for t in (1, 16, 100, 255, 480):
+                assert ask(0, 480 - t, t, h2) == 0
+            L.hwkv_cache_free(h2)
+    call = lambda *a: L.hwkv_prefill_attn_split_bytes(h1, *a, ctypes.byref(r))
+    assert call(2, 0, 1) == hw.EINVAL and call(0, -1, 1) == hw.EINVAL and call(0, 0, -1) == hw.EINVAL
+    assert call(0, 39999, 2) == hw.ECAPACITY and call(0, 2 ** 62, 2 ** 62) == hw.ECAPACITY
+    assert L.hwkv_prefill_attn_split_bytes(h1, 0, 0, 1, None) == hw.EINVAL
+    # the call itself: errors of hwkv_prefill_attn_ws, and unaligned partials
+    sc = ctypes.c_float(0.1)
+    bad = L.hwkv_prefill_attn_split(h1, 0, 0, 0, 1, FAKE, FAKE, FAKE, sc, FAKE, None, 0, FAKE + 4,
+                                    1 << 30, None)
+    assert bad == hw.EINVAL
+    assert L.hwkv_prefill_attn_split(h1, 0, 0, 3, 1, FAKE, FAKE, FAKE, sc, FAKE, None, 0, FAKE,
+                                     1 << 30, None) == hw.ESTATE
+    L.hwkv_cache_free(h1)
+
+
+def test_no_call_makes_a_stream_wait_for_another(hw):
+    out = subprocess.run(["nm", "-D", "--undefined-only", hw.LIB_PATH], capture_output=True,
+                         text=True, check=True).stdout
+    assert "hipLaunchKernel" in out and "hipStreamWaitEvent" not in out
+
+
 def test_prefill_sample_rows_rule():
     cfg = W.CONFIGS["prefill128k"]
     rows = W.prefill_sample_rows(cfg)
