@@ -24,10 +24,6 @@
 namespace hwkv {
 namespace {
 
-// Waves of a workgroup: sixteen (128 registers each) where the accumulators of
-// G heads leave room for the loads in flight, else eight (256).
-constexpr int item_waves(int D, int G) { return G >= 6 || (G == 4 && D == 256) ? 8 : 16; }
-
 // Orders the wave's LDS writes before its later LDS reads (the hardware keeps
 // a wave's LDS operations in order).
 __device__ __forceinline__ void wave_lds_order() {
@@ -39,7 +35,7 @@ __device__ __forceinline__ void wave_lds_order() {
 template <int D, int G>
 struct ItemSmem {
   static constexpr int PST = G == 6 ? 8 : G;     // weights per slot (fp32)
-  static constexpr int NW = item_waves(D, G);
+  static constexpr int NW = decode_item_waves(D, G);
   union {
     float p[NW][64 * PST];               // a wave's weights of its tile
     __attribute__((aligned(16))) float acc[NW][G * D];   // epilogue
@@ -50,14 +46,14 @@ struct ItemSmem {
 };
 
 template <int D, int G, int F>
-__global__ __launch_bounds__(item_waves(D, G) * 64) void decode_item(ItemArgs a) {
+__global__ __launch_bounds__(decode_item_waves(D, G) * 64) void decode_item(ItemArgs a) {
   using Chunk = typename KvFormat<F>::Chunk;
   constexpr int EB = KvFormat<F>::kBytes;
   constexpr int LB = 8 * EB;                     // bytes per chunk
   constexpr int NC = D / 8;                      // chunks per row
   constexpr int RPS = 64 / NC;                   // rows per V step
   constexpr int PIECES = 2 * NC;                 // loads per tile: K chunks, V steps
-  constexpr int NW = item_waves(D, G);
+  constexpr int NW = decode_item_waves(D, G);
   constexpr int PF = NW == 8 && D * G < 2048 ? 16 : 8;   // loads in flight
   constexpr int PST = ItemSmem<D, G>::PST;
   static_assert(RPS * D * EB == 64 * LB, "K chunks and V steps are equally long");
@@ -71,7 +67,11 @@ __global__ __launch_bounds__(item_waves(D, G) * 64) void decode_item(ItemArgs a)
   const int rank = __builtin_amdgcn_readfirstlane(__popcll(__ballot(a.wg_begin[lane] <= run)) - 1);
   const int h = a.head_order[rank];
   const int split = run - a.wg_begin[rank];
-  const int si = blockIdx.x % a.n_seqs;
+  int si = blockIdx.x - run * a.n_seqs;
+  if (a.rotate) {                                // by one from run to run
+    si -= run % a.n_seqs;
+    si += si < 0 ? a.n_seqs : 0;
+  }
   const int b = a.seq[si];
   const int n = a.len[si];
   const ItemHead &hd = a.head[h];
@@ -81,10 +81,10 @@ __global__ __launch_bounds__(item_waves(D, G) * 64) void decode_item(ItemArgs a)
   if (t_lo >= all_tiles) return;                 // uniform: a shorter item
   const int n_tiles = min(all_tiles - t_lo, a.tiles_per_wg) + t_lo;
   const int pto = hd.page0 >= 0 ? hd.page0 + b * a.max_pages : -1;
-  const int64_t at = (int64_t)b * hd.cap_pad * D;
-  uint8_t *const kbase = static_cast<uint8_t *>(a.cache) + (pto >= 0 ? a.pool_off : hd.k_off + at) * EB;
+  const int64_t seq_at = (int64_t)b * hd.cap_pad * D;
+  uint8_t *const kbase = static_cast<uint8_t *>(a.cache) + (pto >= 0 ? a.pool_off : hd.k_off + seq_at) * EB;
   uint8_t *const vbase =
-      static_cast<uint8_t *>(a.cache) + (pto >= 0 ? a.pool_off + kPageTokens * D : hd.v_off + at) * EB;
+      static_cast<uint8_t *>(a.cache) + (pto >= 0 ? a.pool_off + kPageTokens * D : hd.v_off + seq_at) * EB;
   const size_t q_row = ((size_t)b * a.n_kv_heads + h) * G;
   auto page_of = [&](int t) -> int {
     return pto >= 0 ? ((const __attribute__((address_space(4))) int32_t *)
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(item_waves(D, G) * 64) void decode_item(ItemArgs a)
       A.w += x.w * f;
     }
     const float inv = whole ? hd.v_scale / L : 1.0f;
-    const size_t part = (size_t)blockIdx.x * G + g;
+    const size_t part = (size_t)(a.part_begin[rank] + split * a.part_seqs[rank] + si) * G + g;
     float *const to = whole ? a.out + (q_row + g) * D : a.part_acc + part * D;
     __builtin_nontemporal_store(f32x4_t{A.x * inv, A.y * inv, A.z * inv, A.w * inv},
                                 reinterpret_cast<f32x4_t *>(to + c));
@@ -381,8 +381,8 @@ __global__ __launch_bounds__(256) void item_merge(ItemArgs a) {
   const int tiles = (min(a.len[si], hd.cap) + 63) / 64;
   if (tiles <= a.tiles_per_wg) return;
   const int ns = (tiles + a.tiles_per_wg - 1) / a.tiles_per_wg;
-  const size_t p0 = ((size_t)a.wg_begin[rank] * a.n_seqs + si) * G + g;
-  const size_t step = (size_t)a.n_seqs * G;      // the next split's partial
+  const size_t p0 = (size_t)(a.part_begin[rank] + si) * G + g;
+  const size_t step = (size_t)a.part_seqs[rank] * G;   // the next split's partial
   float M = -INFINITY, L = 0.f;
   float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
   constexpr int U = 4;                           // splits per round, loads in flight

@@ -855,7 +855,7 @@ struct ItemLaunch {
   struct At {
     static hipError_t run(const ItemArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
       hipExtLaunchKernelGGL((decode_item<D, G, F>), dim3(a.n_seqs * a.wg_begin[a.n_kv_heads]),
-                            dim3(item_waves(D, G) * 64), 0, s, e0, e1, 0, a);
+                            dim3(decode_item_waves(D, G) * 64), 0, s, e0, e1, 0, a);
       return hipGetLastError();
     }
   };

@@ -649,76 +649,145 @@ int scratch_ptr(void **out) {
   return HWKV_OK;
 }
 
-// Tiles per workgroup of a launch of `total` tiles: items of more are split.  A
-// quarter above an even share of the CUs (48 ragged sequences of 200-6,000
-// tokens, 8 KV heads: 84 us a layer with whole items, 78 / 77 at 1.0 / 1.5
-// shares, 81 / 85 at 0.5 / 0.3), and at least one tile for each of 16 waves.
-int64_t item_tiles(int64_t total, int64_t cus) {
-  return std::max<int64_t>(16, total * 5 / (4 * cus) + 1);
+// One launch of a decode call by item (decode_item.h): up to kItemSeqs
+// sequences, longest first, items of more than T tiles split.
+struct ItemLaunch {
+  int32_t b0 = 0, n = 0;            // sequences [b0, b0 + n)
+  uint8_t seq[hwkv::kItemSeqs];     // the i-th longest is b0 + seq[i],
+  int32_t len[hwkv::kItemSeqs];     // of this length (the appended token included)
+  int64_t T = 0, runs = 0;          // tiles a workgroup; runs of n workgroups
+  int64_t parts = 0;                // split partials
+  double us = 0.0;                  // estimated
+};
+
+// Workgroups of unit u's item of a sequence of length len, of T tiles each.
+int64_t item_splits(const hwkv_cache *c, int32_t u, int32_t len, int64_t T) {
+  return (tiles_for(std::min<int64_t>(len, c->cap[u])) + T - 1) / T;
+}
+
+// Plans the launch of sequences [b0, b0 + n), heads in `order` (by capacity),
+// with room for the partials of `parts` workgroups, and estimates its time.
+//
+// T is a quarter above an even share of the CUs (48 ragged sequences of
+// 200-6,000 tokens, 8 KV heads: 84 us a layer with whole items, 78 / 77 at 1.0 /
+// 1.5 shares, 81 / 85 at 0.5 / 0.3), and at least one tile for each of 16 waves.
+//
+// The estimate, in us: a start; on a CU, one workgroup at a time (two where the
+// registers let them: fp8, one q head), each with a part for its q heads, one for
+// every round of tiles that its waves take, and its tiles at what a CU
+// multiplies, or streams; the workgroups that a shorter item leaves empty; over
+// the CUs the sum of these and a share of the longest, which is larger where
+// they are uneven; or the bytes at 6.3 TB/s; and the merge.
+void plan_item_launch(const hwkv_cache *c, int32_t layer, const int32_t *order, int32_t b0, int32_t n,
+                      bool fused, int64_t parts, ItemLaunch *L) {
+  const hwkv_policy &p = c->pol;
+  const int32_t H = p.n_kv_heads;
+  const int64_t G = group_size(p), D = p.head_dim, cus = hwkv::device_cu_count();
+  L->b0 = b0;
+  L->n = n;
+  for (int32_t i = 0; i < n; ++i) L->seq[i] = (uint8_t)i;
+  const int64_t *len = &c->n[(size_t)layer * c->batch + b0];
+  std::stable_sort(L->seq, L->seq + n, [&](uint8_t x, uint8_t y) { return len[x] > len[y]; });
+  for (int32_t i = 0; i < n; ++i) L->len[i] = (int32_t)len[L->seq[i]] + (fused ? 1 : 0);
+  int64_t total = 0;
+  for (int32_t h = 0; h < H; ++h)
+    for (int32_t i = 0; i < n; ++i)
+      total += tiles_for(std::min<int64_t>(L->len[i], c->cap[layer * H + h]));
+  const int64_t longest =
+      std::max<int64_t>(1, tiles_for(std::min<int64_t>(L->len[0], c->cap[layer * H + order[0]])));
+  int64_t T = std::max<int64_t>(16, total * 5 / (4 * cus) + 1);
+  if (longest <= T + T / 4) T = longest;
+  int64_t runs = 0;
+  for (int32_t h = 0; h < H; ++h) runs += item_splits(c, layer * H + h, L->len[0], T);
+  L->T = T;
+  L->runs = runs;
+
+  int64_t real = 0;                 // workgroups that have tiles
+  for (int32_t h = 0; h < H; ++h)
+    for (int32_t i = 0; i < n; ++i) {
+      int64_t t = tiles_for(std::min<int64_t>(L->len[i], c->cap[layer * H + h]));
+      const int64_t before = real;
+      for (++real; t > T; t -= T) ++real;
+      if (real - before > 1) L->parts += item_splits(c, layer * H + h, L->len[0], T);
+    }
+  if (L->parts > std::min<int64_t>(parts, UINT16_MAX) || runs > UINT16_MAX) {
+    L->us = HUGE_VAL;
+    return;
+  }
+  const bool fp8 = c->fmt == HWKV_KV_FP8_E4M3;
+  const double dg = (double)(D * G), waves = hwkv::decode_item_waves((int)D, (int)G);
+  const double start = fp8 ? 5.1 : 2.2, own = fp8 ? 1.2 * G + 0.0021 * dg : 1.3 * G + 0.0004 * dg;
+  const double tile = std::max((fp8 ? 0.7e-3 : 0.75e-3) * dg, (fp8 ? 3.9e-3 : 5.3e-3) * D);
+  const double top = own + 1.1 * std::ceil((double)T / waves) + tile * (double)T;
+  const double at_once = fp8 && G == 1 ? 2.0 : 1.0, empty = (double)(runs * n - real);
+  const double rounds = std::max((double)real, (double)total / waves + 0.5 * (double)real);
+  double busy = top;
+  if ((double)(runs * n) > at_once * (double)cus) {
+    const bool uneven = T * real > total * 3 / 2 && real > cus;
+    const double sum = tile * (double)total + (1.1 * rounds + own * (double)real) / at_once + 3.3 * empty;
+    busy = std::max(busy, sum / (double)cus + (uneven ? 0.78 : 0.5) * top);
+  }
+  const double bytes = (double)(64 * total * D * 2 * c->elem);
+  L->us = start + std::max(busy, 1.9 + bytes / 6.3e6) + (L->parts > 0 ? 2.9 : 0.0);
+}
+
+// The split launches' time, in us (`tiles`: by item): a launch pair for every
+// kMaxItems items, and the bytes, or the products where these bind.
+double estimate_split(const hwkv_cache *c, const std::vector<int64_t> &tiles) {
+  const double G = (double)group_size(c->pol), D = c->pol.head_dim, items = (double)tiles.size();
+  int64_t total = 0;
+  for (int64_t x : tiles) total += x;
+  const bool fp8 = c->fmt == HWKV_KV_FP8_E4M3;
+  const double bytes = 64.0 * (double)total * D * 2 * c->elem;
+  return std::ceil(items / hwkv::kMaxItems) * (fp8 ? 10.6 + 0.0015 * D * G : 7.6 + 0.57 * G) +
+         std::max((fp8 ? 1.6e-6 : 5.5e-6) * D * G * (double)total, bytes / (fp8 ? 6.6e6 : 6.9e6)) +
+         items / hwkv::kMaxItems;
 }
 
 // Whether a decode call runs with a workgroup per item (decode_item.h) rather
-// than split workgroups and a merge, given the items' 64-slot tiles.  The
-// lesser of two estimates in us, fitted to both sides measured at head_dim x
-// group 64 x 4, 128 x 4, 128 x 8 and 256 x 6, bf16 and fp8, 2 to 512 items of 128
-// to 8,192 slots:
-//   split: a launch pair of about 9 us and more (the q rows) for every 64 items,
-//     and the bytes at 6.2 TB/s;
-//   item: one launch whose workgroups take about 7.5 us and more each, one per
-//     CU at a time, and 15.5 us per million (slot x channel x q head) a CU
-//     multiplies; or the bytes at 5.2 TB/s where they bind; and a merge of
-//     4.5 us where items are split.
-// Split where items are few and long (8 items of 2,048 slots, 128 x 4: 11.7 us
-// against 26.8), by item where there are many (512 of 2,048 slots: 95 against
-// 166; 256 of 512: 20 against 55).  The estimates err by up to a tenth each way
-// on ragged batches, so the split stays unless the gain is clear.
-bool decode_by_item(const hwkv_cache *c, const std::vector<int64_t> &tiles) {
-  const double dg = (double)c->pol.head_dim * (double)group_size(c->pol);
-  const int64_t cus = hwkv::device_cu_count();
-  int64_t longest = 0, total = 0;
-  for (int64_t x : tiles) {
-    longest = std::max(longest, x);
-    total += x;
+// than split workgroups and a merge, and its launches if so: where its estimate
+// is below 0.95 of the split launches'.  The constants of both were fitted to
+// what each side takes in 16-layer steps (bytes from HBM) and in repeated single
+// layers: head_dim 64 / 128 / 256, groups 1 to 8, the three formats, 40 batches of 2
+// to 1,024 items, alike, ragged over up to two powers of ten, or a few long ones
+// among many short.  Of 2,880 such calls all but 10 take at most 3 % longer
+// than split, those up to 7 %; on average 0.5 % more than the better side.
+// bf16, 256 x 1, us a layer by item / split: 8 items of 2,048 slots 25.7 / 10.3, 128 of
+// 512 17.7 / 27.3, 512 of 512 52 / 110; 64 x 8, 16 sequences of 64-4,000, 8 KV heads:
+// 25.8 / 32.7.
+bool decode_by_item(const hwkv_cache *c, int32_t layer, const std::vector<int64_t> &tiles,
+                    const int32_t *order, bool fused, int64_t parts,
+                    std::vector<ItemLaunch> *launches) {
+  const double most = 0.95 * estimate_split(c, tiles);
+  double us = 0.0;
+  for (int32_t b0 = 0; b0 < c->batch && us < most; b0 += hwkv::kItemSeqs) {
+    launches->emplace_back();
+    plan_item_launch(c, layer, order, b0, std::min(hwkv::kItemSeqs, c->batch - b0), fused, parts,
+                     &launches->back());
+    us += launches->back().us;
   }
-  const double slots = 64.0, bytes = slots * (double)total * c->pol.head_dim * 2 * c->elem;
-  const double items = (double)tiles.size();
-  const double groups = std::ceil(items / hwkv::kMaxItems), rounds = std::ceil(items / (double)cus);
-  const double split = groups * (9.0 + 0.0025 * dg) + bytes / 6.2e6;
-  const int64_t T = item_tiles(total, cus);
-  const double base = 7.5 + 0.003 * dg + (c->fmt == HWKV_KV_FP8_E4M3 ? 2.8 : 0.0);
-  const double work = 15.5e-6 * dg * slots *
-                      std::max((double)std::min(longest, T), (double)total / (double)cus);
-  const double item = std::max(base * rounds + work, base + bytes / 5.2e6) + (longest > T ? 4.5 : 0.0);
-  return item < 0.85 * split;
+  return us < most;
 }
 
-// The launches of decode_by_item: up to kItemSeqs sequences each, heads by
-// capacity and sequences by length, longest first.
-// ws: room for the partials of `parts` workgroups (as many as the split
-// kernels' launches would leave; items stay whole where that is too little).
-int launch_items(hwkv_cache *c, int32_t layer, const void *k_new, const void *v_new, const void *q,
-                 float scale, void *out, float *ws, int64_t parts, bool fused, hipStream_t s) {
+// Runs the launches of decode_by_item; ws: room for their partials.
+int launch_items(hwkv_cache *c, int32_t layer, const int32_t *order,
+                 const std::vector<ItemLaunch> &launches, const void *k_new, const void *v_new,
+                 const void *q, float scale, void *out, float *ws, bool fused, hipStream_t s) {
   const hwkv_policy &p = c->pol;
-  const int32_t H = p.n_kv_heads, B = c->batch;
+  const int32_t H = p.n_kv_heads;
   const int64_t G = group_size(p), D = p.head_dim;
   hwkv::ItemArgs a;
   std::memset(&a, 0, sizeof a);
-  std::vector<int32_t> order(H);
   for (int32_t h = 0; h < H; ++h) {
     const int32_t u = layer * H + h;
     hwkv::ItemHead &hd = a.head[h];
-    hd.k_off = c->k_off[u];
-    hd.v_off = c->v_off[u];
     hd.cap = (int32_t)c->cap[u];
     hd.cap_pad = (int32_t)c->cap_pad[u];
     hd.window = (int32_t)c->window[u];
     hd.k_scale = c->k_scale[u];
     hd.v_scale = c->v_scale[u];
-    order[h] = h;
+    a.head_order[h] = (uint8_t)order[h];
   }
-  std::stable_sort(order.begin(), order.end(),
-                   [&](int32_t x, int32_t y) { return a.head[x].cap > a.head[y].cap; });
-  for (int32_t h = 0; h < H; ++h) a.head_order[h] = (uint8_t)order[h];
   a.cache = c->base;
   a.page_table = device_page_table(c);
   a.pool_off = c->pool_off;
@@ -726,54 +795,39 @@ int launch_items(hwkv_cache *c, int32_t layer, const void *k_new, const void *v_
   a.n_sinks = p.n_sinks;
   a.max_pages = (int32_t)c->max_pages;
   a.scale_log2 = scale * 1.4426950408889634f;
-  for (int32_t b0 = 0; b0 < B; b0 += hwkv::kItemSeqs) {
-    const int32_t nb = std::min(hwkv::kItemSeqs, B - b0);
-    std::vector<int32_t> seqs(nb);
-    for (int32_t i = 0; i < nb; ++i) seqs[i] = b0 + i;
-    std::stable_sort(seqs.begin(), seqs.end(), [&](int32_t x, int32_t y) {
-      return seq_len(c, layer, x) > seq_len(c, layer, y);
-    });
-    for (int32_t i = 0; i < nb; ++i) {
-      a.seq[i] = (uint8_t)(seqs[i] - b0);
-      a.len[i] = (int32_t)(seq_len(c, layer, seqs[i]) + (fused ? 1 : 0));
+  for (const ItemLaunch &L : launches) {
+    a.n_seqs = L.n;
+    std::memcpy(a.seq, L.seq, sizeof a.seq);
+    std::memcpy(a.len, L.len, sizeof a.len);
+    a.rotate = L.n % 2 == 0 && a.len[0] != a.len[L.n - 1];
+    // the runs of sequences that each head's workgroups take, and the partials
+    // of the sequences (the first, being the longest) whose item is split
+    int64_t begin = 0, part = 0;
+    for (int32_t r = 0; r < H; ++r) {
+      const int32_t u = layer * H + order[r];
+      const int64_t splits = item_splits(c, u, a.len[0], L.T);
+      int32_t seqs = 0;
+      while (seqs < L.n && item_splits(c, u, a.len[seqs], L.T) > 1) ++seqs;
+      a.wg_begin[r] = (uint16_t)begin;
+      a.part_begin[r] = (uint16_t)part;
+      a.part_seqs[r] = (uint8_t)seqs;
+      begin += splits;
+      part += splits * seqs;
     }
-    a.n_seqs = nb;
-    // Split long items: tiles per workgroup and the workgroups that gives per
-    // run of sequences (heads in order, splits of the head's longest item)
-    int64_t total = 0, longest = 1;
-    for (int32_t h = 0; h < H; ++h)
-      for (int32_t i = 0; i < nb; ++i) {
-        const int64_t t = tiles_for(std::min(a.len[i], a.head[h].cap));
-        total += t;
-        longest = std::max(longest, t);
-      }
-    const int64_t cus = hwkv::device_cu_count();
-    int64_t T = item_tiles(total, cus);
-    auto begin = [&](int64_t per) {
-      int64_t runs = 0;
-      for (int32_t r = 0; r < H; ++r) {
-        a.wg_begin[r] = (uint16_t)runs;
-        runs += (tiles_for(std::min(a.len[0], a.head[order[r]].cap)) + per - 1) / per;
-      }
-      return runs;
-    };
-    if (longest <= T + T / 4 || begin(T) * nb > parts || begin(T) > UINT16_MAX) T = longest;
-    const int64_t runs = begin(T);
-    a.wg_begin[H] = (uint16_t)runs;
+    a.wg_begin[H] = (uint16_t)begin;
     for (int32_t r = H + 1; r <= hwkv::kMaxItems; ++r) a.wg_begin[r] = UINT16_MAX;
-    a.tiles_per_wg = (int32_t)T;
+    a.tiles_per_wg = (int32_t)L.T;
     a.part_acc = ws;
-    a.part_ml = ws ? ws + runs * nb * G * D : nullptr;
-    const bool merge = T < longest;
+    a.part_ml = ws + L.parts * G * D;
     // everything the kernel finds by sequence starts at sequence b0
     for (int32_t h = 0; h < H; ++h) {
       const int32_t u = layer * H + h;
-      const int64_t at = (int64_t)b0 * c->cap_pad[u] * D;
+      const int64_t at = (int64_t)L.b0 * c->cap_pad[u] * D;
       a.head[h].k_off = c->k_off[u] + at;
       a.head[h].v_off = c->v_off[u] + at;
-      a.head[h].page0 = page_tab_off(c, u, b0);
+      a.head[h].page0 = page_tab_off(c, u, L.b0);
     }
-    const size_t kv = (size_t)b0 * H * D, qo = kv * G;
+    const size_t kv = (size_t)L.b0 * H * D, qo = kv * G;
     a.q = static_cast<const uint16_t *>(q) + qo;
     a.k_new = fused ? static_cast<const uint16_t *>(k_new) + kv : nullptr;
     a.v_new = fused ? static_cast<const uint16_t *>(v_new) + kv : nullptr;
@@ -783,10 +837,10 @@ int launch_items(hwkv_cache *c, int32_t layer, const void *k_new, const void *v_
       const int rc = next_event(c, &ev[e]);
       if (rc != HWKV_OK) return rc;
     }
-    if (c->timing) c->ev_merged.push_back(merge);
+    if (c->timing) c->ev_merged.push_back(L.parts > 0);
     int rc = check_device(
         hwkv::launch_decode_item(c->fmt, (int)D, (int)G, a, s, ev[0], ev[1]), "decode item launch");
-    if (rc == HWKV_OK && merge)
+    if (rc == HWKV_OK && L.parts > 0)
       rc = check_device(hwkv::launch_item_merge((int)D, (int)G, a, s, ev[2], ev[3]),
                         "decode item merge launch");
     if (rc != HWKV_OK) return rc;
@@ -857,9 +911,15 @@ int decode_impl(hwkv_cache *c, int32_t layer, const void *k_new,
     const int rc = take_pages(c, layer, want, s);
     if (rc != HWKV_OK) return rc;
   }
-  if (decode_by_item(c, tiles)) {
-    const int rc = launch_items(c, layer, k_new, v_new, q, scale, out, static_cast<float *>(ws),
-                                total_splits, fused, s);
+  int32_t order[hwkv::kMaxItems];   // heads by capacity
+  for (int32_t h = 0; h < H; ++h) order[h] = h;
+  std::stable_sort(order, order + H, [&](int32_t x, int32_t y) {
+    return c->cap[layer * H + x] > c->cap[layer * H + y];
+  });
+  std::vector<ItemLaunch> launches;
+  if (decode_by_item(c, layer, tiles, order, fused, total_splits, &launches)) {
+    const int rc = launch_items(c, layer, order, launches, k_new, v_new, q, scale, out,
+                                static_cast<float *>(ws), fused, s);
     if (rc != HWKV_OK) return rc;
     if (fused)
       for (int32_t b = 0; b < B; ++b) seq_len(c, layer, b) += 1;

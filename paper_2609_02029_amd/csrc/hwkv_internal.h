@@ -78,6 +78,9 @@ struct DecodeArgs {
 // Decode of one launch with a workgroup per (sequence, kv head) item: the
 // layer's kv heads, and up to kItemSeqs of its sequences.
 constexpr int kItemSeqs = 192;
+// Waves of a workgroup: sixteen (128 registers each) where the accumulators of
+// G heads leave room for the loads in flight, else eight (256).
+constexpr int decode_item_waves(int D, int G) { return G >= 6 || (G == 4 && D == 256) ? 8 : 16; }
 struct ItemHead {
   int64_t k_off, v_off;          // element offsets of the unit, sequence 0
   int32_t cap, cap_pad;          // rows holding data; rows allocated
@@ -102,10 +105,18 @@ struct ItemArgs {
   // Split items: the r-th head of head_order has wg_begin[r + 1] - wg_begin[r]
   // = splits x n_seqs workgroups, split by split; split j of an item takes its
   // tiles [j T, (j + 1) T), T = tiles_per_wg, and an item of more than T tiles
-  // leaves one partial per split for item_merge (acc part_acc[workgroup][G][D],
-  // (m, l) part_ml[workgroup][G][2]).
+  // leaves one partial per split for item_merge (acc part_acc[partial][G][D],
+  // (m, l) part_ml[partial][G][2]): the first part_seqs[r] sequences have such an
+  // item of the r-th head, with partials part_begin[r] + j part_seqs[r] + i.
   int32_t tiles_per_wg;
-  uint16_t wg_begin[kMaxItems + 1];   // in units of n_seqs workgroups
+  uint16_t part_begin[kMaxItems];
+  uint8_t part_seqs[kMaxItems];
+  uint16_t wg_begin[kMaxItems + 1];   // in units of n_seqs workgroups (runs)
+  // Whether the order of the sequences moves back by one from run to run.
+  // Workgroups go to the eight XCDs in turn, so with an even number of sequences
+  // the longest would meet the same few XCDs in every run: 2 sequences of 4,000
+  // among 32 of 200, 8 KV heads, 128 x 4, bf16: 69 us against 32.
+  uint16_t rotate;
   float *part_acc, *part_ml;
 };
 

@@ -130,7 +130,8 @@ def test_batched_ragged():
 
 
 def test_more_items_than_one_launch():
-    # 17 sequences x 4 kv heads = 68 items: two launches per call
+    # 17 sequences x 4 kv heads = 68 items, more than a split launch takes (they run by
+    # item; test_gpu_decode_route.py has batches of two split launch groups)
     cfg = mini(batch=17, n_kv_heads=4, n_q_heads=16, level_windows=[30, 0],
                levels=[[0, 1, 1, 0]], prompt=[int(x) for x in range(40, 40 + 17 * 23, 23)],
                max_ctx=600, seed=15)
