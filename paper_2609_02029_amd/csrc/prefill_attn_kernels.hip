@@ -55,10 +55,13 @@
 // the first tile, its mask and the output: the arguments come in two rounds of
 // scalar loads, q and the first two tiles' loads are in flight together, a
 // partly visible tile is masked by bits (keep_rows), the rows go out through
-// LDS (store_rows), and one to two tiles run without the phase shift.  64
-// tokens of 8 heads, head_dim 128, keys 64 / 128 / 256 / 512: 13.3 / 15.0 /
-// 17.7 / 22.9 -> 10.8 / 13.0 / 15.3 / 20.0 us; a prompt of 2,901 tokens in 2
-// layers with its first decode step: 338 -> 307 us.
+// LDS (store_rows; few columns directly), and one to two tiles run without the
+// phase shift.  Against a loop without phases a launch of one block of columns
+// (8 heads, head_dim 64 / 128 / 256, us in a replayed graph) takes: 16 tokens into an
+// empty sequence, group 1, 4.1 / 4.5 / 5.5 -> 5.0 / 5.4 / 6.5; 64 tokens, group 4,
+// 6.1 / 9.0 / 15.5 -> 6.6 / 9.5 / 14.7; 256 tokens 11.1 / 15.2 / 24.4 -> 10.5 / 15.0 /
+// 22.8; 512 tokens 17.7 / 23.1 / 38.8 -> 15.4 / 20.4 / 33.0.  (Issuing a call takes the
+// host 9 us.)
 //
 // Data movement.  K and V tiles go from global memory straight into LDS
 // (buffer_load_dwordx4 ... lds: lane i of an instruction fills bytes
@@ -789,6 +792,7 @@ void prefill_attn(const PrefillAttnArgs a) {
     phase_end();
   }
   if (!late) phase_end();
+  if (!wave_live) return;                          // no column to write
 
   float l_lo, l_hi;
   halves(l, &l_lo, &l_hi);
@@ -813,6 +817,18 @@ void prefill_attn(const PrefillAttnArgs a) {
   constexpr int CH = D > 64 ? 64 : 32, AREA = 128 * CH;
   static_assert(NW / 2 * AREA <= SB && STAGES >= 4, "two stages hold every wave's area");
   // two stages that the other group's last products do not read
+  // Few columns (two waves' at most) go straight from the registers: 64 columns
+  // over four tiles, head_dim 256, 10.4 -> 9.7 us, but 128 columns 9.4 -> 10.5.  (At
+  // head_dim 64 the second path costs longer launches more, 2 %.)
+  if (D > 64 && c_last - c_first < 64) {
+    if (c_out <= c_last)
+#pragma unroll
+      for (int x = 0; x < 4 * DB; ++x)
+        *reinterpret_cast<float4 *>(dst + (size_t)row * D + 8 * x + 4 * (lane_now() >> 5)) =
+            make_float4(o[x / 4][4 * (x % 4) + 0] * inv, o[x / 4][4 * (x % 4) + 1] * inv,
+                        o[x / 4][4 * (x % 4) + 2] * inv, o[x / 4][4 * (x % 4) + 3] * inv);
+    return;
+  }
   const int stage = so + (wave < NW / 2 ? SB : 2 * SB);
   store_rows<D, CH>(o, inv, dst, D, row, c_last - wc0,
                 smem + (stage >= STAGES * SB ? stage - STAGES * SB : stage) +
