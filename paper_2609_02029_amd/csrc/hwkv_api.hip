@@ -687,7 +687,8 @@ void plan_item_launch(const hwkv_cache *c, int32_t layer, const int32_t *order, 
   L->n = n;
   for (int32_t i = 0; i < n; ++i) L->seq[i] = (uint8_t)i;
   const int64_t *len = &c->n[(size_t)layer * c->batch + b0];
-  std::stable_sort(L->seq, L->seq + n, [&](uint8_t x, uint8_t y) { return len[x] > len[y]; });
+  std::sort(L->seq, L->seq + n,
+            [&](uint8_t x, uint8_t y) { return len[x] != len[y] ? len[x] > len[y] : x < y; });
   for (int32_t i = 0; i < n; ++i) L->len[i] = (int32_t)len[L->seq[i]] + (fused ? 1 : 0);
   int64_t total = 0;
   for (int32_t h = 0; h < H; ++h)
@@ -913,8 +914,9 @@ int decode_impl(hwkv_cache *c, int32_t layer, const void *k_new,
   }
   int32_t order[hwkv::kMaxItems];   // heads by capacity
   for (int32_t h = 0; h < H; ++h) order[h] = h;
-  std::stable_sort(order, order + H, [&](int32_t x, int32_t y) {
-    return c->cap[layer * H + x] > c->cap[layer * H + y];
+  std::sort(order, order + H, [&](int32_t x, int32_t y) {
+    const int64_t cx = c->cap[layer * H + x], cy = c->cap[layer * H + y];
+    return cx != cy ? cx > cy : x < y;
   });
   std::vector<ItemLaunch> launches;
   if (decode_by_item(c, layer, tiles, order, fused, total_splits, &launches)) {
