@@ -78,6 +78,9 @@ def test_every_hot_kernel_is_present(kernel_table):
                  "decode_mfma<128, 8>",
                  "prefill_attn<256, 8, 0>", "prefill_attn<128, 8, 0>", "prefill_attn<64, 8, 0>",
                  "prefill_attn<256, 8, 1>", "prefill_attn<128, 8, 1>", "prefill_attn<64, 8, 1>",
+                 "prefill_merge<256, 8>", "prefill_merge<128, 8>", "prefill_merge<64, 8>",
+                 "decode_item<256, 8, 0>", "decode_item<128, 4, 1>", "decode_item<64, 1, 2>",
+                 "item_merge<256, 8>", "item_merge<64, 1>",
                  "replay_attn<256, 8>", "replay_merge<256>", "prefill_write<256, 0>",
                  "append_token<256, 2>"]:
         assert name in kernel_table, sorted(kernel_table)
@@ -103,3 +106,7 @@ def test_register_budgets(kernel_table):
             if g == 8 or (_f == 1 and g == 6 and d >= 256):
                 budget = 168
             assert vg <= budget, (n, vg)
+        # decode by item: sixteen wavefronts of 128 registers a CU, or eight of 256
+        if n.startswith("decode_item<"):
+            d, g, _f = (int(x) for x in n[n.index("<") + 1:-1].split(","))
+            assert vg <= (256 if g >= 6 or (g == 4 and d == 256) else 128), (n, vg)
