@@ -239,10 +239,7 @@ __host__ __device__ inline int prefill_tiles(int KT, int ta, int tb, int S, int 
   return (S + KT - 1) / KT + (tb - lo + KT) / KT;
 }
 
-#ifndef HWKV_PREFILL_WAVES
-#define HWKV_PREFILL_WAVES 8
-#endif
-constexpr int kPrefillWaves = HWKV_PREFILL_WAVES;
+constexpr int kPrefillWaves = 8;   // two groups of four
 
 // Launchers (return the launch status).  D in {64, 128, 256}; G in
 // {1, 2, 4, 6, 8}; fmt one of the HWKV_KV_* formats.  Non-null events e0, e1
