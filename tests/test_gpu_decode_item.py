@@ -1,7 +1,8 @@
 """Decode with a workgroup per (sequence, KV head) item (batches of many short
 items): parity over head dims, groups and formats at the edges of tiles, of a
 workgroup's waves and of the windows, and over more sequences than one launch
-takes."""
+takes.  (test_gpu_decode_route.py checks which batches run by
+item, and their long items.)"""
 import numpy as np
 import pytest
 import torch
