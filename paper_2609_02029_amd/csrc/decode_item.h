@@ -12,8 +12,10 @@
 // lane with PF in flight, running on into the wave's next tile, as in
 // decode_split: q.k with one lane per slot (q from LDS, one address for every
 // lane; bf16 pairs in v_dot2_f32_bf16 -- fp8 codes widen to bf16 exactly -- and
-// binary16 pairs in v_dot2_f32_f16), p.v with a lane on 8 channels of a row and
-// fp32 weights.
+// binary16 pairs in v_dot2_f32_f16; four partial logits a head over 16-bit keys),
+// p.v with a lane on 8 channels of a row and fp32 weights.  Against 64 bits its rms
+// error is 1.02 times decode_split's on average (0.88 to 1.18 over 42 shapes; 1.29
+// with one chain of products a logit), and 0.09 times decode_mfma's over fp8.
 //
 // What bounds it: launch and latency for short items; for long ones what one
 // CU can stream.  Figures stand at the rule that chooses it (hwkv_api.hip).

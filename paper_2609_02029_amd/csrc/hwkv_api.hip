@@ -390,8 +390,9 @@ struct PrefillPlan {
 // launch lasts about as long as its longest block or as all tiles spread over
 // the CUs, whichever is more; splits of T tiles run in k rounds of at most
 // one per CU, each with its own start and its partial to write and merge
-// (kSplitCost tiles a round), and the merge launch and the event after it take
-// about as long as kMergeCost tiles (8 us of 1.6 us).
+// (kSplitCost tiles a round), and the merge launch takes about as long as
+// kMergeCost tiles (8 us of 1.6 us, a tile of 64 keys at head_dim 128; the same
+// numbers serve the other head_dims).
 constexpr int64_t kSplitCost = 6, kMergeCost = 5, kSplitLeast = 4, kSplitRounds = 2;
 // Tiles of a head's first column block and a bound of every block's.
 struct HeadTiles {

@@ -35,10 +35,11 @@
 // other has the vector ALU.  (With every wavefront in the same phase, as the
 // barrier per tile of a plain loop leaves them, the two units take turns.)
 // Measured on one chip, before -> after, 8K tokens at 120K of context, head_dim
-// 256, windows {2K, 8K, 32K, full}: 7.30 -> 6.67 ms, 1,170 -> 1,285 TFLOP/s
-// (the matrix cores busy 0.60 -> 0.73 of the cycles, at a clock that falls
-// with the load); 4K tokens at 12K, head_dim 64, binary16: 508 -> 329 us, bound
-// by the exponentials and the arithmetic around them.  The softmax phase also
+// 256, windows {2K, 8K, 32K, full}: 7.34 -> 6.89 ms, 1,168 -> 1,245 TFLOP/s (7.06 to
+// 7.34 -> 6.64 to 7.07 over several; the matrix cores busy 0.575 -> 0.667 of 14.2 ->
+// 12.3 million cycles, at a clock that falls with the load); 4K tokens at 12K,
+// head_dim 64, binary16: 508 -> 319 us, bound by the exponentials and the
+// arithmetic around them.  The softmax phase also
 // issues the loads of tile i + 2 into the fourth stage of LDS; tile addresses
 // are kept as runs (issue_loads), since a lane's address worked out per tile
 // cost as much as a third of the softmax.
@@ -47,9 +48,12 @@
 // context), or with most of its keys in one head, leaves CUs idle: the host
 // then splits the key tiles of every block over several workgroups
 // (tiles_per_split), whose partials prefill_merge adds up.  512 tokens at 48K
-// of context, head_dim 128: 1,717 -> 153 us with both changes (206 by this
-// one); 1,999 tokens at 30K over fp8, head_dim 256: 1,450 -> 672 (801).
-// A split is made only where it also pays for the merge launch.
+// of context, head_dim 128: 1,718 -> 143 us with both changes (206 by this
+// one); 1,999 tokens at 30K over fp8, head_dim 256: 1,451 -> 677 (801).
+// A split is made only where it also pays for the merge launch, and where the
+// caller gives room for the partials.  The weights are rounded to 16 bits under a
+// split's own shift, so a split call's outputs differ from the unsplit one's by up
+// to 2e-3 of their norm (bf16), as far from 64-bit results as they (1.7e-3).
 //
 // Short launches (a few tiles) are bound by the latency of the chain before
 // the first tile, its mask and the output: the arguments come in two rounds of
@@ -61,7 +65,9 @@
 // empty sequence, group 1, 4.1 / 4.5 / 5.5 -> 5.0 / 5.4 / 6.5; 64 tokens, group 4,
 // 6.1 / 9.0 / 15.5 -> 6.6 / 9.5 / 14.7; 256 tokens 11.1 / 15.2 / 24.4 -> 10.5 / 15.0 /
 // 22.8; 512 tokens 17.7 / 23.1 / 38.8 -> 15.4 / 20.4 / 33.0.  (Issuing a call takes the
-// host 9 us.)
+// host 9 us.)  What the shortest lose is the last phase, whose S^T goes unused, a
+// second block of keys, and barriers; leaving out the barrier after the softmax
+// where the second group has no columns changed nothing.
 //
 // Data movement.  K and V tiles go from global memory straight into LDS
 // (buffer_load_dwordx4 ... lds: lane i of an instruction fills bytes
