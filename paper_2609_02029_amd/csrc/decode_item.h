@@ -155,10 +155,13 @@ __global__ __launch_bounds__(decode_item_waves(D, G) * 64) void decode_item(Item
   __syncthreads();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 
+  // m starts at a finite number, so that a tile whose logits are all -inf has zero
+  // weights (decode_split's workgroups take a tile together, and the later ones
+  // meet a finite shift; here every wave has a first tile of its own)
   float m[G], l[G], acc[G][8];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    m[g] = -INFINITY;
+    m[g] = -3e38f;
     l[g] = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;

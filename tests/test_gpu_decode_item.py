@@ -94,3 +94,33 @@ def test_small_products_beside_a_large_one(D, G, fmt, big):
     ref = 1.0 / (1.0 + np.exp(-delta))
     assert float((out - ref).abs().max()) <= 0.25 * (lost + ulp)
     assert 0.25 * (delta - lost - ulp) > 0.25 * (lost + ulp)   # all of them lost would show
+
+
+# Tiles whose logits are all -inf (infinite keys) weigh nothing, wherever a wave
+# meets them.
+@pytest.mark.parametrize("D,G,fmt", [(64, 1, "bf16"), (128, 4, "bf16"), (256, 8, "f16")])
+@pytest.mark.parametrize("lo,hi", [(0, 64), (64, 128), (128, 512), (320, 448)])
+def test_tiles_of_minus_infinity(D, G, fmt, lo, hi):
+    B, H, n = 64, 4, 512
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)
+    pol = hwkv.policy_set(1, H, H * G, D, 0, [0], [[0] * H])
+    cache = hwkv.cache_alloc(pol, B, n + 8, kv_format=fmt)
+    k, v, q = rnd(n, H, D), rnd(n, H, D), rnd(B, H * G, D)
+    q[:, :, 0] = -1.0
+    k[lo:hi, :, 0] = float("inf")
+    for b in range(B):
+        hwkv.prefill_write(cache, 0, b, 0, k, v)
+    out = torch.empty(B, H * G, D, device="cuda")
+    ws = torch.empty(hwkv.decode_workspace_bytes(cache), dtype=torch.uint8, device="cuda")
+    hwkv.decode_timing(cache, True)
+    hwkv.decode_attn(cache, 0, q, 0.1, out, ws)
+    torch.cuda.synchronize()
+    assert hwkv.decode_timing_read(cache)[2] == 1     # by item
+    cache.free()
+    keep = torch.tensor([i for i in range(n) if not lo <= i < hi], device="cuda")
+    as64 = (lambda x: x.to(torch.float16).double()) if fmt == "f16" else (lambda x: x.double())
+    kk, vv = as64(k[keep]).permute(1, 2, 0).contiguous(), as64(v[keep]).permute(1, 0, 2).contiguous()
+    z = torch.matmul(q.double().reshape(B, H, G, D), kk) * 0.1
+    ref = torch.matmul(torch.softmax(z, -1), vv).reshape(B, H * G, D)
+    assert float((out - ref).abs().max()) <= 2e-5 * 8.0   # fp32 sums, |v| < 8
