@@ -759,22 +759,21 @@ double estimate_split(const hwkv_cache *c, const std::vector<int64_t> &tiles) {
 // 25.8 / 32.7.
 bool decode_by_item(const hwkv_cache *c, int32_t layer, const std::vector<int64_t> &tiles,
                     const int32_t *order, bool fused, int64_t parts,
-                    std::vector<ItemLaunch> *launches) {
+                    ItemLaunch *launches) {
   const double most = 0.95 * estimate_split(c, tiles);
   double us = 0.0;
-  for (int32_t b0 = 0; b0 < c->batch && us < most; b0 += hwkv::kItemSeqs) {
-    launches->emplace_back();
+  for (int32_t b0 = 0; b0 < c->batch && us < most; b0 += hwkv::kItemSeqs, ++launches) {
     plan_item_launch(c, layer, order, b0, std::min(hwkv::kItemSeqs, c->batch - b0), fused, parts,
-                     &launches->back());
-    us += launches->back().us;
+                     launches);
+    us += launches->us;
   }
   return us < most;
 }
 
 // Runs the launches of decode_by_item; ws: room for their partials.
 int launch_items(hwkv_cache *c, int32_t layer, const int32_t *order,
-                 const std::vector<ItemLaunch> &launches, const void *k_new, const void *v_new,
-                 const void *q, float scale, void *out, float *ws, bool fused, hipStream_t s) {
+                 const ItemLaunch *launches, const void *k_new, const void *v_new, const void *q,
+                 float scale, void *out, float *ws, bool fused, hipStream_t s) {
   const hwkv_policy &p = c->pol;
   const int32_t H = p.n_kv_heads;
   const int64_t G = group_size(p), D = p.head_dim;
@@ -797,10 +796,11 @@ int launch_items(hwkv_cache *c, int32_t layer, const int32_t *order,
   a.n_sinks = p.n_sinks;
   a.max_pages = (int32_t)c->max_pages;
   a.scale_log2 = scale * 1.4426950408889634f;
-  for (const ItemLaunch &L : launches) {
+  for (int32_t b0 = 0; b0 < c->batch; b0 += hwkv::kItemSeqs, ++launches) {
+    const ItemLaunch &L = *launches;
     a.n_seqs = L.n;
-    std::memcpy(a.seq, L.seq, sizeof a.seq);
-    std::memcpy(a.len, L.len, sizeof a.len);
+    std::memcpy(a.seq, L.seq, L.n * sizeof a.seq[0]);
+    std::memcpy(a.len, L.len, L.n * sizeof a.len[0]);
     a.rotate = L.n % 2 == 0 && a.len[0] != a.len[L.n - 1];
     // the runs of sequences that each head's workgroups take, and the partials
     // of the sequences (the first, being the longest) whose item is split
@@ -919,8 +919,10 @@ int decode_impl(hwkv_cache *c, int32_t layer, const void *k_new,
     const int64_t cx = c->cap[layer * H + x], cy = c->cap[layer * H + y];
     return cx != cy ? cx > cy : x < y;
   });
-  std::vector<ItemLaunch> launches;
-  if (decode_by_item(c, layer, tiles, order, fused, total_splits, &launches)) {
+  ItemLaunch one;                   // (a batch of one launch: nothing from the heap)
+  std::vector<ItemLaunch> several(B > hwkv::kItemSeqs ? (B - 1) / hwkv::kItemSeqs + 1 : 0);
+  ItemLaunch *const launches = several.empty() ? &one : several.data();
+  if (decode_by_item(c, layer, tiles, order, fused, total_splits, launches)) {
     const int rc = launch_items(c, layer, order, launches, k_new, v_new, q, scale, out,
                                 static_cast<float *>(ws), fused, s);
     if (rc != HWKV_OK) return rc;
